@@ -4,6 +4,7 @@
 """
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import subprocess
 import sys
@@ -13,12 +14,14 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 SOURCES = [os.path.join(CSRC, f) for f in ("eqb_api.hip", "margin.hip", "select.hip", "balance.hip", "variants.hip",
                                           "layer_noalloc.hip")]
-# The routing kernels are compiled on their own, without IEEE mode: their
+# The routing kernels are compiled on their own (one object per expert count,
+# in parallel: every fan-out has its own unrolled kernel), without IEEE mode: their
 # float maxima and medians then need no NaN quieting, which lets the compiler
 # fold each DPP group maximum into one instruction and schedule around its
 # wait states.  Their operands are keys and finite scores, never NaN (finite
 # inputs are a precondition of the library).
 ROUTE_SOURCE = os.path.join(CSRC, "route.hip")
+ROUTE_EXPERTS = (256, 128, 64, 32, 16, 8)
 ROUTE_FLAGS = ["-mno-amdgpu-ieee", "-fno-honor-nans"]
 OUT = os.path.join(HERE, "libeqb.so")
 ARCH = os.environ.get("EQB_OFFLOAD_ARCH", "gfx950")
@@ -69,15 +72,22 @@ def build(verbose: bool = False, extra=(), out: str = OUT, sanitize: bool = Fals
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     extra = list(extra) + (SANITIZE_FLAGS if sanitize else [])
     tmp = out + ".tmp"
-    route_obj = out + ".route.o"
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
     compile_flags = [f for f in FLAGS if f != "-shared"]
+    jobs = [([*compile_flags, *ROUTE_FLAGS, f"-DEQB_ROUTE_E={e}"], ROUTE_SOURCE, f"{out}.route{e}.o")
+            for e in ROUTE_EXPERTS]
+    jobs += [(compile_flags, src, f"{out}.{os.path.basename(src)}.o") for src in SOURCES]
+    objs = [obj for _, _, obj in jobs]
     try:
-        _run([hipcc, *compile_flags, *ROUTE_FLAGS, *extra, *inc, "-c", ROUTE_SOURCE, "-o", route_obj], verbose)
-        _run([hipcc, *FLAGS, *extra, *inc, *SOURCES, "-x", "none", route_obj, "-o", tmp], verbose)
+        with concurrent.futures.ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as pool:
+            for f in [pool.submit(_run, [hipcc, *flags, *extra, *inc, "-c", src, "-o", obj], verbose)
+                      for flags, src, obj in jobs]:
+                f.result()
+        _run([hipcc, *FLAGS, *extra, *objs, "-o", tmp], verbose)
     finally:
-        if os.path.exists(route_obj):
-            os.remove(route_obj)
+        for obj in objs:
+            if os.path.exists(obj):
+                os.remove(obj)
     os.replace(tmp, out)
     return out
 

@@ -25,9 +25,6 @@ struct PartTable {
   int64_t off[EQB_MAX_PARTITIONS + 1];
   int32_t P;
   int32_t nsub = 1;
-  // Claim counters of the partitions' dynamic tails (one int32 per
-  // partition, 256 bytes apart, zero at launch), or null: see block_plan.
-  int32_t* pool = nullptr;
   // Coarse count slabs of 16-bit counters (the layer's route sweep, where no
   // slab can receive more than 65,535 rows): slab [E/2][256][2], the counters
   // of experts 2m and 2m+1 for kappa bin k side by side at (m*256 + k)*2,
@@ -185,6 +182,11 @@ constexpr int kKeyTop = (int)0x7F800000u;    // +inf: above every key
 __device__ __forceinline__ int key_max(int a, int b) {
   int r;
   asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ int key_min(int a, int b) {
+  int r;
+  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
 }
 __device__ __forceinline__ int key_med3(int a, int b, int c) {
@@ -402,77 +404,6 @@ __device__ __forceinline__ int64_t wave_uniform(int64_t x) {
 __device__ __forceinline__ void block_rows(int64_t T, int64_t rows_per_block, int64_t* r0, int64_t* r1) {
   *r0 = (int64_t)blockIdx.x * rows_per_block;
   *r1 = (*r0 + rows_per_block < T) ? *r0 + rows_per_block : T;
-}
-
-// Dynamic tails (the one-call layer's route sweep).  Compute units do not
-// sweep at one speed (the blocks of a launch finish up to ~5% apart), so a
-// static split waits for the slowest.  With pt.pool set, the blocks of a
-// launch are dealt out to the partitions in proportion to their rows (block
-// b serves partition p when floor(nb off[p] / T) <= b < floor(nb off[p+1] /
-// T); the host checks that every non-empty partition gets a block), and a
-// partition's blocks form groups of at most kGroupBlocks, each taking a share
-// of the partition's rows in proportion to its blocks.  A group keeps the
-// last 1/kPoolDiv of its rows (at most kPoolMax) as a pool and splits the rest
-// into contiguous static ranges, one per block; once a wave has finished its
-// block's range it claims pool chunks from the group's counter until none is
-// left.  Groups keep the claims on one counter few.  Static ranges are
-// flushed every kSegPool rows, so a block's last static segment plus any pool
-// rows it takes stay below the 16-bit LDS counters' limit.  Groups of 8 with
-// half their rows pooled (at most 49,152: a large workload's group of 8 keeps
-// 37.5% back and its blocks' 10,240-row static ranges stay one segment)
-// measured 2-3.5% faster per step than groups of 16 pooling an eighth
-// (4,194,304 tokens), and 1-2% at 1.5-2 M tokens; groups of 4, and pools of
-// a quarter or a third, fell in between.
-constexpr int64_t kPoolMax = 49152;
-constexpr int64_t kPoolDiv = 2;
-constexpr int kGroupBlocks = 8;
-constexpr int64_t kSegPool = kSegMax - kPoolMax;
-// A group's claim counter is indexed by the group's first block and sits on
-// its own 128-byte line; pool mode is used for grids of at most
-// kPoolCounters blocks.
-constexpr int kPoolStride = 32;
-constexpr int kPoolCounters = 1024;
-
-struct BlockPlan {
-  int64_t r0, r1;     // the block's static rows
-  int64_t q0, q1;     // its group's pool (pool mode)
-  int p;              // the partition served (pool mode), else -1
-  int ctr;            // its group's counter (pool mode)
-  bool pool;
-};
-
-inline __host__ __device__ int64_t pool_block_start(const PartTable& pt, int64_t T, int64_t nb, int p) {
-  return nb * pt.off[p] / T;
-}
-
-__device__ __forceinline__ BlockPlan block_plan(const PartTable& pt, int64_t T, int64_t rows_per_block) {
-  BlockPlan w;
-  w.p = -1;
-  w.ctr = 0;
-  w.q0 = w.q1 = 0;
-  w.pool = pt.pool != nullptr;
-  if (!w.pool) {
-    block_rows(T, rows_per_block, &w.r0, &w.r1);
-    return w;
-  }
-  const int64_t nb = gridDim.x, b = blockIdx.x;
-  // block b serves p when nb off[p] < (b + 1) T <= nb off[p+1]
-  int p = 0;
-  while (p < pt.P - 1 && nb * pt.off[p + 1] < (b + 1) * T) ++p;
-  const int64_t b0 = pool_block_start(pt, T, nb, p), m = pool_block_start(pt, T, nb, p + 1) - b0;
-  const int64_t n = pt.off[p + 1] - pt.off[p], i = b - b0;
-  const int64_t gb0 = (i / kGroupBlocks) * kGroupBlocks;
-  const int64_t gb1 = gb0 + kGroupBlocks < m ? gb0 + kGroupBlocks : m;
-  const int64_t g0 = pt.off[p] + n * gb0 / m, g1 = pt.off[p] + n * gb1 / m;   // the group's rows
-  const int64_t gn = g1 - g0, q = gn / kPoolDiv < kPoolMax ? gn / kPoolDiv : kPoolMax;
-  const int64_t s = gn - q, j = i - gb0, mg = gb1 - gb0;
-  w.p = p;
-  w.ctr = (int)(b0 + gb0);
-  w.r0 = g0 + s * j / mg;
-  w.r1 = g0 + s * (j + 1) / mg;
-  w.q0 = g0 + s;
-  w.q1 = g1;
-  return w;
 }
 
 }  // namespace eqb

@@ -54,6 +54,8 @@ inline int layer_part_blocks(int) { return kPartCUs; }
 
 // *slab16_used: the coarse counts went to 16-bit slabs (see PartTable).
 eqb_status launch_route(const RouteArgs& a, hipStream_t s, bool* slab16_used = nullptr);
+template <int E>
+eqb_status launch_route_e(const RouteArgs& a, hipStream_t s, bool* slab16_used);   // route.hip, one object per E
 // *part_used: the number of per-block images the fine pass wrote (0 when it
 // added its counts to a.hist).
 eqb_status launch_margin(bool fine, const MarginArgs& a, hipStream_t s, int* part_used = nullptr);
@@ -67,7 +69,7 @@ eqb_status launch_select(int pass, const int32_t* hist, int P, int E, int64_t r,
 eqb_status launch_layer_selects(int pass, int32_t* hist, int P, int nsub, int E, int64_t r, int32_t* sel_hi,
                                 int64_t* rank_in_bin, int32_t* sel_lo, uint16_t* q_bf16, float* b_next,
                                 int32_t* hist_sum, int32_t* load_acc, int32_t* load_out, int32_t* status,
-                                int32_t* pool_reset, hipStream_t s, bool slab16 = false);
+                                hipStream_t s, bool slab16 = false);
 // The fine selection of a layer from the fine pass's per-block images
 // (nparts of them), then the centring and status as launch_layer_selects(2).
 eqb_status launch_layer_select_parts(const uint32_t* part, int nparts, int E, int32_t* sel_hi,
@@ -118,10 +120,14 @@ struct LayerWorkspace {
   int32_t* sel_hi;        // [E]
   int32_t* sel_lo;        // [E]
   int64_t* rank_in_bin;   // [E]
-  int32_t* pool;          // claim counters of the route sweep's dynamic tails (kPoolCounters, kPoolStride apart)
+  int32_t* tickets;       // counters of finished blocks (kTicketBytes reserved)
   uint32_t* part;         // [part_blocks, part_words(E)] or null
   int part_blocks;
 };
+
+// Reserved for tickets.  Far more than they take: the workspace keeps the size
+// that callers have allocated by.
+constexpr size_t kTicketBytes = 128 << 10;
 
 inline size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
@@ -136,8 +142,7 @@ inline size_t layer_workspace(void* base, int E, int P, LayerWorkspace* w, bool 
   const size_t load = align256((size_t)P * E * sizeof(int32_t));
   const size_t sel = align256((size_t)E * sizeof(int32_t));
   const size_t rib = align256((size_t)E * sizeof(int64_t));
-  const size_t pool = (size_t)kPoolCounters * kPoolStride * sizeof(int32_t);
-  const size_t zero = 2 * hist + load + 2 * sel + rib + pool;
+  const size_t zero = 2 * hist + load + 2 * sel + rib + kTicketBytes;
   const size_t part = with_part ? align256((size_t)layer_part_blocks(E) * part_words(E) * sizeof(uint32_t)) : 0;
   if (base && w) {
     char* p = static_cast<char*>(base);
@@ -148,7 +153,7 @@ inline size_t layer_workspace(void* base, int E, int P, LayerWorkspace* w, bool 
     w->sel_hi = reinterpret_cast<int32_t*>(p + 2 * hist + load);
     w->sel_lo = reinterpret_cast<int32_t*>(p + 2 * hist + load + sel);
     w->rank_in_bin = reinterpret_cast<int64_t*>(p + 2 * hist + load + 2 * sel);
-    w->pool = reinterpret_cast<int32_t*>(p + 2 * hist + load + 2 * sel + rib);
+    w->tickets = reinterpret_cast<int32_t*>(p + 2 * hist + load + 2 * sel + rib);
     w->part = with_part ? reinterpret_cast<uint32_t*>(p + zero) : nullptr;
     w->part_blocks = with_part ? layer_part_blocks(E) : 0;
   }
@@ -205,28 +210,6 @@ inline void grid_for(int64_t T, int rows_per_step, int blocks_per_cu, int* block
 }
 
 inline eqb_status launch_status() { return hipGetLastError() == hipSuccess ? EQB_OK : EQB_ERR_HIP; }
-
-// The partition table for a launch of `blocks` blocks: pool mode (pt.pool)
-// is kept only when every non-empty partition gets a block of its own under
-// block_plan's proportional deal and a block's share is at least min_rows
-// (small batches gain nothing from it), else the table falls back to static
-// ranges.
-inline PartTable pool_table(const PartTable& pt, int64_t T, int blocks, int64_t min_rows) {
-  PartTable out = pt;
-  if (out.pool == nullptr) return out;
-  if (blocks > kPoolCounters || T < min_rows * blocks) {
-    out.pool = nullptr;
-    return out;
-  }
-  for (int p = 0; p < pt.P; ++p) {
-    if (pt.off[p + 1] > pt.off[p] &&
-        pool_block_start(pt, T, blocks, p + 1) <= pool_block_start(pt, T, blocks, p)) {
-      out.pool = nullptr;
-      break;
-    }
-  }
-  return out;
-}
 
 // Most rows any count slab of a route launch with static ranges receives:
 // block b covers rows [b * rows_per_block, (b + 1) * rows_per_block) and adds

@@ -14,10 +14,11 @@
 // scores order correctly; the key's sum takes -0 in b as +0, so a score of
 // -0 keys as +0 and the two zeros share one run of keys.
 // K+1 extraction rounds then take the group maximum of the list heads with
-// DPP and pop the winner; the largest head left is rank K+1.  A lane whose
-// list runs dry is refilled below its last key (generic-K variant) or, in
-// the unrolled variants, scanned once for its next key, and a row whose
-// rounds missed a key is extracted again with refilled lists.  Key order is
+// DPP and pop the winner (unrolled: every fan-out has its own kernel; a loop
+// over K took 28.4 us where the unrolled rounds take 21 for 99,991 tokens of
+// E = 128, K = 5); the largest head left is rank K+1.  A lane whose list runs
+// dry is scanned once for its next key, and a row whose rounds missed a key
+// is extracted again with refilled lists.  Key order is
 // score order except between scores that agree in their top 24 bits;
 // extraction continues until the last key leaves the top-24-bit run of rank
 // K, the winners' exact scores are recomputed from z and b, and a row whose
@@ -31,20 +32,31 @@
 namespace eqb {
 
 constexpr int kRmax = 16;              // extracted ranks kept per row
-// Sorted keys kept per lane.  With eight lanes per row (E >= 64) a lane
-// holds five or more of a row's top K+1 keys in about one wave in fourteen
-// of the large E = 256, K = 8 workload; such lanes are settled by one scan
-// for their next key (below), which costs less than a sixth list level in
-// every row.  Narrower rows (fewer lanes each holding a larger share of
-// the top keys) keep six.
-template <int E> constexpr int kListOf = E >= 64 ? 5 : 6;
+// Sorted keys kept per lane: the rounds pop at most K+1 keys of a lane and
+// look at one more, and a lane holds N = E/G keys in all, so min(N, K + 2)
+// never runs dry.  Fewer levels cost less per element (one instruction each);
+// a row whose lane does run dry is done again by the full path, so the depth
+// is the one at which that happens in about 1% of rows of random logits.
+// Lanes per row.  A row costs a wave its extraction rounds and outputs once,
+// whatever the lanes it is spread over, so few lanes with more experts each
+// are cheaper per element until their longer lists cost more: four lanes
+// instead of eight took the layer of 262,144 tokens, E = 64, K = 6 from 47.4
+// to 44.6 us; at E = 128 (N = 32, lists of seven) it is even, and at E = 32 two
+// lanes instead of four change nothing.
+template <int E> struct FastCfg { static constexpr int G = E >= 128 ? 8 : E >= 32 ? 4 : E / 8; };
+template <int E, int K>
+constexpr int list_depth() {
+  constexpr int G = FastCfg<E>::G, N = E / G;
+  constexpr int d = G == 8 ? (K <= 8 ? 5 : K <= 11 ? 6 : 7) : G == 4 ? (K <= 4 ? 5 : K <= 6 ? 6 : K <= 8 ? 7 : 8) : 8;
+  constexpr int m = N < K + 2 ? N : K + 2;
+  return d < m ? d : m;
+}
 constexpr int kFastKmax = kRmax - 2;
 // Block of the fast kernel: 12 waves, three per SIMD, so that a wave may hold
 // up to 168 VGPRs (with 16 waves the cap of 128 forces spills).
 constexpr int kRouteBlock = 768;
 constexpr int kRouteWaves = kRouteBlock / 64;
 
-template <int E> struct FastCfg { static constexpr int G = E >= 64 ? 8 : E / 8; };
 constexpr int kBiasPad = 32;           // words between the rotated bias copies beyond E
 
 // The BF16 logit z of an extracted key.  The key holds the top 24 bits H of
@@ -161,9 +173,26 @@ __device__ __forceinline__ void list_insert(int (&L)[n], int x) {
   L[0] = key_max(L[0], x);
 }
 
+// Insert key x as the i-th key of a list being built (the levels below i are
+// still empty): i + 1 instructions while i < n.
+template <int n>
+__device__ __forceinline__ void list_insert_at(int (&L)[n], int x, int i) {
+  if (i >= n) {
+    list_insert(L, x);
+  } else if (i == 0) {
+    L[0] = x;
+  } else {
+    L[i] = key_min(L[i - 1], x);
+#pragma unroll
+    for (int j = n - 1; j > 0; --j)
+      if (j < i) L[j] = key_med3(L[j - 1], L[j], x);
+    L[0] = key_max(L[0], x);
+  }
+}
+
 template <int E, int KT>
 __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
-    const uint16_t* __restrict__ z, const float* __restrict__ b, int64_t T, int Kdyn,
+    const uint16_t* __restrict__ z, const float* __restrict__ b, int64_t T,
     int32_t* __restrict__ topk_idx, float* __restrict__ topk_score, float* __restrict__ tau,
     int32_t* __restrict__ load, int32_t* __restrict__ hist, const PartTable pt,
     int64_t rows_per_block) {
@@ -171,12 +200,12 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
   constexpr int N = E / G;              // experts per lane
   constexpr int NQ = N / 4;             // 8-byte pieces per lane and row
   constexpr int R = 64 / G;             // rows per wave
-  constexpr int ROWS = kRouteWaves * R;      // rows per block step
-  constexpr int RSLOT = (kRmax + G - 1) / G;
+  constexpr int RSLOT = (kRmax + G - 1) / G;  // rank slots per lane, staged rows
+  constexpr int HSLOT = (KT + G) / G;         // rank slots per lane, ranks 0..K
+  constexpr int K = KT;
   static_assert(N % 4 == 0 && N >= 8, "layout");
-  static_assert(KT == 0 || KT + 2 <= E, "K+2 keys must exist");
-  constexpr int kList = kListOf<E>;
-  const int K = KT > 0 ? KT : Kdyn;
+  static_assert(KT >= 1 && KT < E && KT <= kFastKmax, "K+1 keys exist and fit the rank buffer");
+  constexpr int kList = list_depth<E, KT>();
 
   __shared__ __align__(16) uint32_t sh_hist[fast_hist_words<E>()];
   __shared__ uint32_t sh_load[E];
@@ -187,7 +216,7 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
   // the 64 banks) would put every row's reads on the same 32 banks.
   __shared__ float sh_bk[NQ][E + kBiasPad];
   __shared__ uint2 sh_rank[kRouteWaves][R][kRmax];   // (score bits, zbits << 16 | e) in rank order
-  __shared__ int sh_pool_spent;                       // the group's pool has run out (pool mode)
+  __shared__ uint32_t sh_step;                        // next unclaimed wave step of the segment
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane % G, r = lane / G;
@@ -226,15 +255,14 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
   // The first step of the block's first segment (as for_each_segment will
   // cut it) is loaded before the LDS set-up, so that its latency passes while
   // the histogram is zeroed and the bias is staged.
-  const BlockPlan plan = block_plan(pt, T, rows_per_block);
-  const int64_t r0 = plan.r0, r1 = plan.r1;
-  const int64_t seg_max = plan.pool ? kSegPool : kSegMax;
+  int64_t r0, r1;
+  block_rows(T, rows_per_block, &r0, &r1);
   uint2 buf[NQ];
   if (r0 < r1) {
     int p = 0;
     while (p < pt.P - 1 && pt.off[p + 1] <= r0) ++p;
     int64_t end = pt.off[p + 1] < r1 ? pt.off[p + 1] : r1;
-    if (end - r0 > seg_max) end = r0 + seg_max;
+    if (end - r0 > kSegMax) end = r0 + kSegMax;
     load_step(buf, z + wave_uniform(r0) * E, 0, (uint32_t)(end - r0));
   }
 
@@ -242,7 +270,7 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
   for (int w = threadIdx.x; w < fast_hist_words<E>() / 4; w += kRouteBlock)
     reinterpret_cast<uint4*>(sh_hist)[w] = make_uint4(0, 0, 0, 0);
   int fits = 1, bzero = 1;
-  if (threadIdx.x == 0) sh_pool_spent = 0;
+  if (threadIdx.x == 0) sh_step = kRouteWaves;
   for (int e = threadIdx.x; e < E; e += kRouteBlock) {
     sh_load[e] = 0;
     const float bv = b[e];
@@ -314,8 +342,6 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
     refill(raw);
     int L[kList];
 #pragma unroll
-    for (int j = 0; j < kList; ++j) L[j] = kKeyNone;
-#pragma unroll
     for (int q = 0; q < NQ; ++q) {
       // The next piece's bias is read while this piece is inserted; the
       // scheduling barrier keeps the compiler from sinking the read to its use.
@@ -324,7 +350,8 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
       __builtin_amdgcn_sched_barrier(0);
       const uint32_t ipk = idxpk(q);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) list_insert(L, key_of(zf[q * 4 + i], pick(bq, i), ipk, i));
+      for (int i = 0; i < 4; ++i)
+        list_insert_at(L, key_of(zf[q * 4 + i], pick(bq, i), ipk, i), q * 4 + i);
       bq = bn;
     }
 
@@ -340,225 +367,186 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
     bool staged = false, slow = false;
     int nrank = 0;
     float tv = 0.0f;          // tau of this lane's row (common rows)
-    int rk[RSLOT];
-    uint32_t zown[RSLOT];
+    int rk[HSLOT];
+    uint32_t zown[HSLOT];
 #pragma unroll
-    for (int s = 0; s < RSLOT; ++s) {
+    for (int s = 0; s < HSLOT; ++s) {
       rk[s] = kKeyNone;
       zown[s] = 0;
     }
 
-    if constexpr (KT > 0) {
-      int mK = kKeyNone, prev = kKeyNone;
-      bool near = false;      // two adjacent extracted keys share their top 24 bits
-      const int tail = L[kList - 1];   // the smallest key a lane can pop
+    int mK = kKeyNone, prev = kKeyNone;
+    bool near = false;      // two adjacent extracted keys share their top 24 bits
+    const int tail = L[kList - 1];   // the smallest key a lane can pop
 #pragma unroll
-      for (int k = 0; k <= KT; ++k) {
-        const int M = group_max_key<G>(L[0]);
-        pop(M);
-        rk[k / G] = (g == k % G) ? M : rk[k / G];
-        if (k > 0) near |= ((uint32_t)(M ^ prev) < 256u);
-        prev = M;
-        if (k == KT) mK = M;
+    for (int k = 0; k <= K; ++k) {
+      const int M = group_max_key<G>(L[0]);
+      pop(M);
+      rk[k / G] = (g == k % G) ? M : rk[k / G];
+      if (k > 0) near |= ((uint32_t)(M ^ prev) < 256u);
+      prev = M;
+      if (k == K) mK = M;
+    }
+    // Rank K+1 is the largest list head left.  Whether it shares the top 24
+    // bits of rank K is read off the heads directly; the rest of each list
+    // is not needed past this point (a row that extends its run rebuilds
+    // its lists), so the last rounds' pops only shift the entries that
+    // later rounds read.
+    // A lane whose list ran dry popped all of its kList keys and has no
+    // head: its next key is the largest of its keys below the last one it
+    // popped, found by one scan of its logits.  If that key ranks above
+    // rank K, the rounds missed it and the row is extracted again; if not,
+    // it is the lane's head.  A head of -inf (no key left) never matches:
+    // no finite key has the top 24 bits of -inf.
+    int hk = L[0];
+    bool missed = false;
+    if (__builtin_expect(__any(L[0] == kKeyNone), 0)) {
+      const bool dry_lane = L[0] == kKeyNone;
+      int nxt = kKeyNone;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const float4 bq = bias4(q);
+        const uint32_t ipk = idxpk(q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int x = key_of(zf[q * 4 + i], pick(bq, i), ipk, i);
+          nxt = key_lt(x, tail) ? key_max(nxt, x) : nxt;
+        }
       }
-      // Rank K+1 is the largest list head left.  Whether it shares the top 24
-      // bits of rank K is read off the heads directly; the rest of each list
-      // is not needed past this point (a row that extends its run rebuilds
-      // its lists), so the last rounds' pops only shift the entries that
-      // later rounds read.
-      // A lane whose list ran dry popped all of its kList keys and has no
-      // head: its next key is the largest of its keys below the last one it
-      // popped, found by one scan of its logits.  If that key ranks above
-      // rank K, the rounds missed it and the row is extracted again; if not,
-      // it is the lane's head.  A head of -inf (no key left) never matches:
-      // no finite key has the top 24 bits of -inf.
-      int hk = L[0];
-      bool missed = false;
-      if (__builtin_expect(__any(L[0] == kKeyNone), 0)) {
-        const bool dry_lane = L[0] == kKeyNone;
-        int nxt = kKeyNone;
+      hk = dry_lane ? nxt : hk;
+      missed = dry_lane && key_lt(mK, nxt);
+    }
+    const int head = ((uint32_t)(hk ^ mK) < 256u) ? 1 : 0;
+    const int rowflag = group_max_i32<G>(missed ? 2 : head);
+    // z of the experts at this lane's ranks, recovered from their keys.
+    // Every slot's bias is read before any is used, so the LDS latency is
+    // paid once; one wave-wide test sends the failed recoveries to memory.
+    int es[HSLOT];
+    bool use[HSLOT], ok[HSLOT];
+    float bks[HSLOT];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          const float4 bq = bias4(q);
-          const uint32_t ipk = idxpk(q);
+    for (int s = 0; s < HSLOT; ++s) {
+      use[s] = valid && s * G + g <= K;
+      // below E for every key of the row; the clamp keeps a row whose
+      // keys cannot be trusted (it goes slow) inside its own logits
+      es[s] = use[s] ? min(255 - (rk[s] & 0xFF), E - 1) : 0;
+      bks[s] = sh_bk[0][es[s]];
+    }
+    bool bad = false;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int x = key_of(zf[q * 4 + i], pick(bq, i), ipk, i);
-            nxt = key_lt(x, tail) ? key_max(nxt, x) : nxt;
+    for (int s = 0; s < HSLOT; ++s) {
+      zown[s] = z_from_key(rk[s], bks[s], &ok[s]);
+      ok[s] = ok[s] | !use[s];
+      bad = bad | !ok[s];
+    }
+    if (__builtin_expect(__any(bad), 0)) {
+      // The few failed recoveries are read one lane at a time with scalar
+      // loads: their wait does not include the vector loads of the next
+      // step, which are still in flight (vector loads complete in order, so
+      // a vector fallback load would wait for all of them).
+#pragma unroll
+      for (int s = 0; s < HSLOT; ++s) {
+        const uint32_t off = (t * (uint32_t)E + (uint32_t)es[s]) * 2u;   // < 2^25
+        uint32_t zl = zown[s];
+        uint64_t need = __ballot(!ok[s]);
+        while (need) {
+          const int l = __builtin_ctzll(need);
+          const uint32_t o = __builtin_amdgcn_readlane(off, l);
+          // the aligned word holding z (seg_z is 16-byte aligned)
+          const uint32_t w = at<const uint32_t>(seg_z, o & ~3u);
+          if (lane == l) zl = (w >> ((o & 2u) * 8u)) & 0xFFFFu;
+          need &= need - 1;
+        }
+        zown[s] = zl;
+      }
+    }
+    const int tauhi = mK >> 8;
+    const bool dry = rowflag == 2;   // the rounds missed a key of a dry lane
+    slow = valid && !bias_ok;
+    staged = valid && !slow && (near || rowflag != 0);
+    nrank = K + 1;
+    // A row is staged when adjacent ranks' keys agree in their top 24 bits
+    // (their order may be wrong) or the run of rank K's top 24 bits
+    // continues past it.  With exact keys such keys hold equal scores, and
+    // for a non-negative rank K (every rank at or above it non-negative)
+    // the index byte already orders them as the exact order does: only a
+    // missed key needs the staged path.
+    if constexpr (decltype(exact)::value) staged = staged && (dry || mK < 0);
+    if (__builtin_expect(__any(staged), 0)) {
+      // stage the keys, extend the run of rank K if it continues, then exact scores
+#pragma unroll
+      for (int s = 0; s < HSLOT; ++s) {
+        const int k = s * G + g;
+        if (staged && k <= K) myrank[k].x = (uint32_t)rk[s];
+      }
+      // the keys past rank K are taken from lists rebuilt below mK, while
+      // they share the top 24 bits of rank K
+      bool ext = staged && rowflag == 1;
+      bool bad = false;           // row-uniform: extraction can no longer be trusted
+      if (__any(ext)) {
+        rebuild(zf, mK, L);
+        for (int k = K + 1; k < kRmax; ++k) {
+          if (!__any(ext)) break;
+          // a lane whose list ran dry may hold the next key
+          const bool dry_now = group_max_i32<G>((int)(L[0] == kKeyNone)) != 0;
+          if (ext && dry_now) {
+            bad = true;
+            ext = false;
           }
-        }
-        hk = dry_lane ? nxt : hk;
-        missed = dry_lane && key_lt(mK, nxt);
-      }
-      const int head = ((uint32_t)(hk ^ mK) < 256u) ? 1 : 0;
-      const int rowflag = group_max_i32<G>(missed ? 2 : head);
-      // z of the experts at this lane's ranks, recovered from their keys.
-      // Every slot's bias is read before any is used, so the LDS latency is
-      // paid once; one wave-wide test sends the failed recoveries to memory.
-      int es[RSLOT];
-      bool use[RSLOT], ok[RSLOT];
-      float bks[RSLOT];
-#pragma unroll
-      for (int s = 0; s < RSLOT; ++s) {
-        use[s] = valid && s * G + g <= KT;
-        // below E for every key of the row; the clamp keeps a row whose
-        // keys cannot be trusted (it goes slow) inside its own logits
-        es[s] = use[s] ? min(255 - (rk[s] & 0xFF), E - 1) : 0;
-        bks[s] = sh_bk[0][es[s]];
-      }
-      bool bad = false;
-#pragma unroll
-      for (int s = 0; s < RSLOT; ++s) {
-        zown[s] = z_from_key(rk[s], bks[s], &ok[s]);
-        ok[s] = ok[s] | !use[s];
-        bad = bad | !ok[s];
-      }
-      if (__builtin_expect(__any(bad), 0)) {
-        // The few failed recoveries are read one lane at a time with scalar
-        // loads: their wait does not include the vector loads of the next
-        // step, which are still in flight (vector loads complete in order, so
-        // a vector fallback load would wait for all of them).
-#pragma unroll
-        for (int s = 0; s < RSLOT; ++s) {
-          const uint32_t off = (t * (uint32_t)E + (uint32_t)es[s]) * 2u;   // < 2^25
-          uint32_t zl = zown[s];
-          uint64_t need = __ballot(!ok[s]);
-          while (need) {
-            const int l = __builtin_ctzll(need);
-            const uint32_t o = __builtin_amdgcn_readlane(off, l);
-            // the aligned word holding z (seg_z is 16-byte aligned)
-            const uint32_t w = at<const uint32_t>(seg_z, o & ~3u);
-            if (lane == l) zl = (w >> ((o & 2u) * 8u)) & 0xFFFFu;
-            need &= need - 1;
-          }
-          zown[s] = zl;
-        }
-      }
-      const int tauhi = mK >> 8;
-      const bool dry = rowflag == 2;   // the rounds missed a key of a dry lane
-      slow = valid && !bias_ok;
-      staged = valid && !slow && (near || rowflag != 0);
-      nrank = KT + 1;
-      // A row is staged when adjacent ranks' keys agree in their top 24 bits
-      // (their order may be wrong) or the run of rank K's top 24 bits
-      // continues past it.  With exact keys such keys hold equal scores, and
-      // for a non-negative rank K (every rank at or above it non-negative)
-      // the index byte already orders them as the exact order does: only a
-      // missed key needs the staged path.
-      if constexpr (decltype(exact)::value) staged = staged && (dry || mK < 0);
-      if (__builtin_expect(__any(staged), 0)) {
-        // stage the keys, extend the run of rank K if it continues, then exact scores
-#pragma unroll
-        for (int s = 0; s < RSLOT; ++s) {
-          const int k = s * G + g;
-          if (staged && k <= KT) myrank[k].x = (uint32_t)rk[s];
-        }
-        // the keys past rank K are taken from lists rebuilt below mK, while
-        // they share the top 24 bits of rank K
-        bool ext = staged && rowflag == 1;
-        bool bad = false;           // row-uniform: extraction can no longer be trusted
-        if (__any(ext)) {
-          rebuild(zf, mK, L);
-          for (int k = KT + 1; k < kRmax; ++k) {
-            if (!__any(ext)) break;
-            // a lane whose list ran dry may hold the next key
-            const bool dry_now = group_max_i32<G>((int)(L[0] == kKeyNone)) != 0;
-            if (ext && dry_now) {
-              bad = true;
-              ext = false;
-            }
-            const int M = group_max_key<G>(L[0]);
-            if (ext) {
-              if (g == 0) myrank[k].x = (uint32_t)M;
-              nrank = k + 1;
-              if ((M >> 8) != tauhi) ext = false;
-            }
-            pop(M);
-          }
-        }
-        bad = bad || ext;           // the run is longer than the rank buffer
-        // Rows whose rounds missed a key (a lane held more of the top K+1
-        // keys than its list) redo the extraction from fresh lists, refilling
-        // a lane's list below its last key whenever it runs dry again (as the
-        // generic-K loop does); only a run longer than the rank buffer still
-        // goes to the exact 64-bit path.
-        bool redo = staged && dry;
-        if (__any(redo)) {
-          if (redo) rebuild(zf, kKeyTop, L);
-          bool done = !redo;
-          int th = 0;
-#pragma unroll 1
-          for (int k = 0; k < kRmax; ++k) {
-            if (!__any(!done)) break;
-            const int M = group_max_key<G>(L[0]);
-            pop(M);
-            const bool dl = (L[0] == kKeyNone) && (M != kKeyNone);
-            if (__any(dl && !done)) {
-              if (dl && !done) rebuild(zf, M, L);
-            }
-            if (!done) {
-              if (M == kKeyNone) {
-                done = true;
-              } else {
-                if (g == 0) myrank[k].x = (uint32_t)M;
-                nrank = k + 1;
-                if (k == K) th = M >> 8;
-                if (k > K && (M >> 8) != th) done = true;   // one key past the run of rank K
-              }
-            }
-          }
-          bad = bad || !done;
-        }
-        slow = slow || bad;
-        staged = staged && !slow;
-        lds_wave_sync();
-#pragma unroll
-        for (int s = 0; s < RSLOT; ++s) {
-          const int k = s * G + g;
-          if (staged && k < nrank) {
-            const int key = (int)myrank[k].x;
-            const int e = 255 - (key & 0xFF);
-            bool ok;
-            uint32_t zb = z_from_key(key, sh_bk[0][e], &ok);
-            if (!ok) zb = seg_z[t * E + e];
-            const uint32_t sb = __float_as_uint(__uint_as_float(zb << 16) + sh_b[e]);
-            myrank[k] = make_uint2(sb, (zb << 16) | (uint32_t)e);
-          }
-        }
-        lds_wave_sync();
-      }
-    } else {
-      bool done = !valid;
-      int tauhi = 0;
-#pragma unroll 1
-      for (int k = 0; k < kRmax; ++k) {
-        if (!__any(!done)) break;
-        const int M = group_max_key<G>(L[0]);
-        pop(M);
-        const bool dry = (L[0] == kKeyNone) && (M != kKeyNone);
-        if (__any(dry && !done)) {
-          if (dry && !done) rebuild(zf, M, L);
-        }
-        if (!done) {
-          if (M == kKeyNone) {
-            done = true;
-          } else {
+          const int M = group_max_key<G>(L[0]);
+          if (ext) {
             if (g == 0) myrank[k].x = (uint32_t)M;
             nrank = k + 1;
-            if (k == K) tauhi = M >> 8;
-            if (k > K && (M >> 8) != tauhi) done = true;   // one key past the run of rank K
+            if ((M >> 8) != tauhi) ext = false;
           }
+          pop(M);
         }
       }
-      slow = valid && (!done || !bias_ok);
-      staged = valid && !slow;
+      bad = bad || ext;           // the run is longer than the rank buffer
+      // Rows whose rounds missed a key (a lane held more of the top K+1
+      // keys than its list) redo the extraction from fresh lists, refilling
+      // a lane's list below its last key whenever it runs dry again (as the
+      // generic-K loop does); only a run longer than the rank buffer still
+      // goes to the exact 64-bit path.
+      bool redo = staged && dry;
+      if (__any(redo)) {
+        if (redo) rebuild(zf, kKeyTop, L);
+        bool done = !redo;
+        int th = 0;
+#pragma unroll 1
+        for (int k = 0; k < kRmax; ++k) {
+          if (!__any(!done)) break;
+          const int M = group_max_key<G>(L[0]);
+          pop(M);
+          const bool dl = (L[0] == kKeyNone) && (M != kKeyNone);
+          if (__any(dl && !done)) {
+            if (dl && !done) rebuild(zf, M, L);
+          }
+          if (!done) {
+            if (M == kKeyNone) {
+              done = true;
+            } else {
+              if (g == 0) myrank[k].x = (uint32_t)M;
+              nrank = k + 1;
+              if (k == K) th = M >> 8;
+              if (k > K && (M >> 8) != th) done = true;   // one key past the run of rank K
+            }
+          }
+        }
+        bad = bad || !done;
+      }
+      slow = slow || bad;
+      staged = staged && !slow;
       lds_wave_sync();
 #pragma unroll
       for (int s = 0; s < RSLOT; ++s) {
         const int k = s * G + g;
         if (staged && k < nrank) {
-          const int e = 255 - (int)(myrank[k].x & 0xFF);
-          const uint32_t zb = seg_z[t * E + e];
+          const int key = (int)myrank[k].x;
+          const int e = 255 - (key & 0xFF);
+          bool ok;
+          uint32_t zb = z_from_key(key, sh_bk[0][e], &ok);
+          if (!ok) zb = seg_z[t * E + e];
           const uint32_t sb = __float_as_uint(__uint_as_float(zb << 16) + sh_b[e]);
           myrank[k] = make_uint2(sb, (zb << 16) | (uint32_t)e);
         }
@@ -628,11 +616,11 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
 
     // ---- outputs: ranks 0..K-1, loads, tau
     const bool fromlds = staged || slow;
-    if (KT > 0 && valid && !fromlds) {
+    if (valid && !fromlds) {
       // rank k is held by lane k % G in slot k / G; its exact score is z + b of that expert
       float tk = 0.0f;
 #pragma unroll
-      for (int s = 0; s < RSLOT; ++s) {
+      for (int s = 0; s < HSLOT; ++s) {
         const int k = s * G + g;
         if (k <= K) {
           const int e = 255 - (rk[s] & 0xFF);
@@ -648,10 +636,8 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
       }
       tv = tk;
     }
-    if constexpr (KT > 0) {
-      // every lane of the row takes tau from the lane holding rank K
-      tv = group_bcast<G, KT % G>(tv, g);
-    }
+    // every lane of the row takes tau from the lane holding rank K
+    tv = group_bcast<G, K % G>(tv, g);
     if (valid && fromlds) {
 #pragma unroll
       for (int s = 0; s < RSLOT; ++s) {
@@ -725,6 +711,7 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
         sh_load[e] = 0;
       }
     }
+    if (threadIdx.x == 0) sh_step = kRouteWaves;
     __syncthreads();
   };
   auto sweep = [&](auto exact) __attribute__((always_inline)) {
@@ -741,61 +728,25 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
     // step was loaded before the LDS set-up.
     if (!first) load_step(buf, seg_z, 0, n);
     first = false;
-    for (uint32_t base = 0; base < n; base += ROWS) {
-      const uint32_t t = base + wave * R + r;
-      process(exact, buf, t, t < n, [&](uint2 (&dst)[NQ]) { load_step(dst, seg_z, base + ROWS, n); });
+    // A wave starts with step `wave` (R rows) and claims each further step
+    // from an LDS counter: the SIMD serves its oldest wave first, so with a
+    // fixed share per wave the waves of a SIMD finish one after another and the
+    // last one runs alone (4,096 rows of E = 128 per block: the first wave
+    // done after 66 us, the last after 96 us).  The claim is issued when a step
+    // starts and read after the step's logits are widened, where the claimed
+    // rows are loaded.
+    for (uint32_t base = wave * R; base < n;) {
+      uint32_t claimed = 0, next = 0;
+      if (lane == 0) claimed = atomicAdd(&sh_step, 1u);
+      const uint32_t t = base + r;
+      process(exact, buf, t, t < n, [&](uint2 (&dst)[NQ]) {
+        next = __builtin_amdgcn_readfirstlane(claimed) * (uint32_t)R;
+        load_rows(dst, seg_z, next, n);
+      });
+      base = next;
     }
-    // in pool mode the last static segment's counts are flushed with the pool's
-    if (!(plan.pool && s1 == r1)) flush_counts(p);
-  }, seg_max);
-  if (plan.pool) {
-    // The group's pool, claimed by single waves in chunks of kChunk rows
-    // (kChunkSteps wave steps).  A wave claims its next chunk when it starts
-    // one and reads the claim at the start of the chunk's last step, whose
-    // refill loads the next chunk's first rows; that read waits only for
-    // loads the step waits for anyway.  A wave that draws past the pool
-    // marks it spent in LDS, and the block's other waves then stop claiming.
-    constexpr uint32_t kChunkSteps = 8;
-    constexpr uint32_t kChunk = (uint32_t)R * kChunkSteps;
-    set_base(plan.q0);
-    const uint32_t nq = (uint32_t)(plan.q1 - plan.q0);
-    const uint32_t nchunks = (nq + kChunk - 1) / kChunk;
-    int32_t* ctr = pt.pool + (int64_t)plan.ctr * kPoolStride;
-    volatile int* spent = &sh_pool_spent;
-    auto claim = [&]() -> uint32_t {
-      uint32_t v = nchunks;
-      if (lane == 0 && *spent == 0) v = (uint32_t)atomicAdd(ctr, 1);
-      return v;
-    };
-    auto take = [&](uint32_t v) -> uint32_t {
-      const uint32_t c = __builtin_amdgcn_readfirstlane(v);
-      if (c >= nchunks && lane == 0) *spent = 1;
-      return c;
-    };
-    uint32_t c = take(claim());
-    uint32_t pend = nchunks;
-    if (c < nchunks) {
-      load_rows(buf, seg_z, c * kChunk, nq);
-      pend = claim();
-    }
-    while (c < nchunks) {
-      uint32_t cn = nchunks;
-#pragma unroll 1
-      for (uint32_t j = 0; j < kChunkSteps; ++j) {
-        const uint32_t wbase = c * kChunk + j * (uint32_t)R;
-        uint32_t next = wbase + (uint32_t)R;
-        if (j + 1 == kChunkSteps) {
-          cn = take(pend);
-          next = cn < nchunks ? cn * kChunk : wbase;
-        }
-        const uint32_t t = wbase + r;
-        process(exact, buf, t, t < nq, [&](uint2 (&dst)[NQ]) { load_rows(dst, seg_z, next, nq); });
-      }
-      c = cn;
-      if (c < nchunks) pend = claim();
-    }
-    flush_counts(plan.p);
-  }
+    flush_counts(p);
+  });
   };
   if (keys_exact) sweep(std::true_type{});
   else sweep(std::false_type{});
@@ -880,63 +831,45 @@ __global__ __launch_bounds__(kBlock) void route_generic_kernel(
 }
 
 // ------------------------------------------------------------- launch ---
-// Dynamic tails only for blocks of at least this many block steps: on
-// shorter ranges the pool's claims cost more than the tail they remove
-// (E = 128 with 4,096 rows per block: 3% slower; E = 256 with 16,384: 2%
-// faster).
-constexpr int64_t kPoolMinSteps = 64;
-
 template <int E, int KT>
 void launch_fast(const RouteArgs& a, hipStream_t s, bool* slab16_used) {
   int blocks;
   int64_t rpb;
   grid_for(a.T, kRouteWaves * (64 / FastCfg<E>::G), 1, &blocks, &rpb);
-  PartTable pt = pool_table(a.pt, a.T, blocks, kPoolMinSteps * kRouteWaves * (64 / FastCfg<E>::G));
-  pt.slab16 = (kSlotHist<E> && a.hist != nullptr && a.slab16_ok && pt.pool == nullptr &&
+  PartTable pt = a.pt;
+  pt.slab16 = (kSlotHist<E> && a.hist != nullptr && a.slab16_ok &&
                slab_rows_bound(pt, rpb) <= kSegMax) ? 1 : 0;
   if (slab16_used) *slab16_used = pt.slab16 != 0;
-  route_fast_kernel<E, KT><<<blocks, kRouteBlock, 0, s>>>(a.z, a.b, a.T, a.K, a.idx, a.score, a.tau, a.load,
+  route_fast_kernel<E, KT><<<blocks, kRouteBlock, 0, s>>>(a.z, a.b, a.T, a.idx, a.score, a.tau, a.load,
                                                      a.hist, pt, rpb);
+}
+
+// Every fan-out up to kFastKmax has its own kernel, the rounds unrolled.
+template <int E, int K>
+eqb_status launch_route_k(const RouteArgs& a, hipStream_t s, bool* slab16_used) {
+  if constexpr (K <= kFastKmax && K < E) {
+    if (a.K == K) {
+      launch_fast<E, K>(a, s, slab16_used);
+      return launch_status();
+    }
+    return launch_route_k<E, K + 1>(a, s, slab16_used);
+  } else {
+    int blocks;
+    int64_t rpb;
+    grid_for(a.T, kWaves * (64 / (E / 8)), 1, &blocks, &rpb);
+    route_generic_kernel<E><<<blocks, kBlock, 0, s>>>(a.z, a.b, a.T, a.K, a.idx, a.score, a.tau, a.load,
+                                                      a.hist, a.pt, rpb);
+    return launch_status();
+  }
 }
 
 template <int E>
 eqb_status launch_route_e(const RouteArgs& a, hipStream_t s, bool* slab16_used) {
   if (slab16_used) *slab16_used = false;
-  if (a.K <= kFastKmax) {
-    // the common MoE fan-outs get a kernel with the rounds unrolled
-    if constexpr (E >= 64) {
-      switch (a.K) {
-        case 1: launch_fast<E, 1>(a, s, slab16_used); return launch_status();
-        case 2: launch_fast<E, 2>(a, s, slab16_used); return launch_status();
-        case 4: launch_fast<E, 4>(a, s, slab16_used); return launch_status();
-        case 6: launch_fast<E, 6>(a, s, slab16_used); return launch_status();
-        case 8: launch_fast<E, 8>(a, s, slab16_used); return launch_status();
-        default: break;
-      }
-    }
-    launch_fast<E, 0>(a, s, slab16_used);
-  } else {
-    int blocks;
-    int64_t rpb;
-    grid_for(a.T, kWaves * (64 / (E / 8)), 1, &blocks, &rpb);
-    PartTable pt = a.pt;
-    pt.pool = nullptr;   // static ranges only
-    route_generic_kernel<E><<<blocks, kBlock, 0, s>>>(a.z, a.b, a.T, a.K, a.idx, a.score, a.tau, a.load,
-                                                      a.hist, pt, rpb);
-  }
-  return launch_status();
+  return launch_route_k<E, 1>(a, s, slab16_used);
 }
 
-eqb_status launch_route(const RouteArgs& a, hipStream_t s, bool* slab16_used) {
-  switch (a.E) {
-    case 8: return launch_route_e<8>(a, s, slab16_used);
-    case 16: return launch_route_e<16>(a, s, slab16_used);
-    case 32: return launch_route_e<32>(a, s, slab16_used);
-    case 64: return launch_route_e<64>(a, s, slab16_used);
-    case 128: return launch_route_e<128>(a, s, slab16_used);
-    case 256: return launch_route_e<256>(a, s, slab16_used);
-    default: return EQB_ERR_UNSUPPORTED;
-  }
-}
+// This file is compiled once per expert count, the objects side by side.
+template eqb_status launch_route_e<EQB_ROUTE_E>(const RouteArgs& a, hipStream_t s, bool* slab16_used);
 
 }  // namespace eqb
