@@ -67,14 +67,14 @@ eqb_status launch_select(int pass, const int32_t* hist, int P, int E, int64_t r,
 
 // slab16: the pass-1 slabs hold 16-bit counters (PartTable::slab16).
 eqb_status launch_layer_selects(int pass, int32_t* hist, int P, int nsub, int E, int64_t r, int32_t* sel_hi,
-                                int64_t* rank_in_bin, int32_t* sel_lo, uint16_t* q_bf16, float* b_next,
+                                int64_t* rank_in_bin, uint16_t* q_bf16, float* b_next,
                                 int32_t* hist_sum, int32_t* load_acc, int32_t* load_out, int32_t* status,
-                                hipStream_t s, bool slab16 = false);
+                                int32_t* ticket, hipStream_t s, bool slab16 = false);
 // The fine selection of a layer from the fine pass's per-block images
 // (nparts of them), then the centring and status as launch_layer_selects(2).
 eqb_status launch_layer_select_parts(const uint32_t* part, int nparts, int E, int32_t* sel_hi,
-                                     int64_t* rank_in_bin, int32_t* sel_lo, uint16_t* q_bf16, float* b_next,
-                                     int32_t* hist_sum, int32_t* status, hipStream_t s);
+                                     int64_t* rank_in_bin, uint16_t* q_bf16, float* b_next,
+                                     int32_t* hist_sum, int32_t* status, int32_t* ticket, hipStream_t s);
 
 eqb_status launch_select_local(int pass, const int32_t* hist, int E, int K, const PartTable& pt,
                                int32_t* sel_hi, int64_t* rank_in_bin, int32_t* sel_lo, uint16_t* q_bf16,
@@ -118,7 +118,6 @@ struct LayerWorkspace {
   int32_t* hist_lo;       // [P,nsub,E,256]
   int32_t* load_acc;      // [P,E]
   int32_t* sel_hi;        // [E]
-  int32_t* sel_lo;        // [E]
   int64_t* rank_in_bin;   // [E]
   int32_t* tickets;       // counters of finished blocks (kTicketBytes reserved)
   uint32_t* part;         // [part_blocks, part_words(E)] or null
@@ -151,7 +150,6 @@ inline size_t layer_workspace(void* base, int E, int P, LayerWorkspace* w, bool 
     w->hist_lo = reinterpret_cast<int32_t*>(p + hist);
     w->load_acc = reinterpret_cast<int32_t*>(p + 2 * hist);
     w->sel_hi = reinterpret_cast<int32_t*>(p + 2 * hist + load);
-    w->sel_lo = reinterpret_cast<int32_t*>(p + 2 * hist + load + sel);
     w->rank_in_bin = reinterpret_cast<int64_t*>(p + 2 * hist + load + 2 * sel);
     w->tickets = reinterpret_cast<int32_t*>(p + 2 * hist + load + 2 * sel + rib);
     w->part = with_part ? reinterpret_cast<uint32_t*>(p + zero) : nullptr;

@@ -79,12 +79,102 @@ __global__ __launch_bounds__(kNBins) void select_coarse_kernel(
   }
 }
 
-template <bool kLocal>
+// Binary64 sum of val[0..E) (E <= 256, 256 threads or more) in ascending
+// order.  The values are BF16 numbers: 8 significant bits each, so while their
+// exponents span at most 36 every partial sum in any order is below 2^(8 + 1 +
+// emax) and a multiple of 2^(emin - 7), 53 bits at most: exact, and equal to the
+// ascending sum.  Then the waves sum in parallel; a wider span (or a NaN) is
+// summed one by one, 256 dependent additions.
+__device__ __forceinline__ double ascending_sum(const double* val, int E, double* sh, int* shx) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (wave < 4) {
+    double x = tid < E ? val[tid] : 0.0;
+    // biased binary64 exponents; zeros do not count
+    const int ex = (int)((__double_as_longlong(x) >> 52) & 0x7FF);
+    int lo = x != 0.0 ? ex : 0x7FF, hi = x != 0.0 ? ex : 0;
+    for (int d = 32; d > 0; d >>= 1) {
+      x += __shfl_xor(x, d);
+      lo = min(lo, __shfl_xor(lo, d));
+      hi = max(hi, __shfl_xor(hi, d));
+    }
+    if (lane == 0) {
+      sh[wave] = x;
+      shx[2 * wave] = lo;
+      shx[2 * wave + 1] = hi;
+    }
+  }
+  __syncthreads();
+  const int lo = min(min(shx[0], shx[2]), min(shx[4], shx[6]));
+  const int hi = max(max(shx[1], shx[3]), max(shx[5], shx[7]));
+  if (hi - lo <= 36) return ((sh[0] + sh[1]) + sh[2]) + sh[3];
+  double acc = 0.0;
+  for (int e = 0; e < E; ++e) acc += val[e];
+  return acc;
+}
+
+// b = b_hat - mean(b_hat) (Eq. 2): the binary64 sum in ascending expert order
+// divided by E, the difference in binary64, one rounding to binary32.  Called
+// by every thread of a block of at least 256, thread e < E with b_hat_e.
+__device__ __forceinline__ void center_block(uint32_t q, int E, float* b_next) {
+  __shared__ double val[256], sh_sum[4];
+  __shared__ int sh_exp[8];
+  const int e = threadIdx.x;
+  if (e < E) val[e] = (double)__uint_as_float(q << 16);
+  __syncthreads();
+  const double mean = ascending_sum(val, E, sh_sum, sh_exp) / (double)E;
+  if (e < E) b_next[e] = (float)(val[e] - mean);
+}
+
+__global__ __launch_bounds__(256) void center_kernel(const uint16_t* __restrict__ q, int E,
+                                                     float* __restrict__ b_next) {
+  center_block(threadIdx.x < E ? q[threadIdx.x] : 0u, E, b_next);
+}
+
+// The end of a layer's fine selection: the last of its blocks to finish centres
+// the bias and writes the status (an expert whose selection failed holds fewer
+// counts than its rank).  A launch of its own for that took 4 to 5 us of every
+// layer.  No block waits for another: each adds itself to the ticket, and the
+// one that completes the count goes on.
+// The blocks sit on XCDs with an L2 each.  Only b_hat passes between them, in
+// agent-scope stores and loads that go past the L2s: the stores have completed
+// (vmcnt) before the block's ticket is drawn.  A release and an acquire fence
+// instead would write back and invalidate a whole L2 in each of the E/2 blocks
+// (70.9 us per layer of 147,456 tokens, E = 256).  Everything else a block
+// leaves behind, it writes alone.
+struct LayerTail {
+  int32_t* ticket = nullptr;   // zero before and after: finished blocks, failed ones counted above bit 16
+  float* b_next = nullptr;
+  int32_t* status = nullptr;
+};
+
+__device__ __forceinline__ void store_bhat(uint16_t* q, uint16_t bits) {
+  __hip_atomic_store(q, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void layer_tail(const LayerTail& tail, bool failed, uint16_t* q, int E) {
+  __shared__ int sh_n;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  const int bad = __syncthreads_or((int)failed) ? 1 << 16 : 0;
+  if (threadIdx.x == 0)
+    sh_n = bad + 1 + __hip_atomic_fetch_add(tail.ticket, bad + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const int n = sh_n;
+  if ((n & 0xFFFF) != (int)gridDim.x) return;
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(tail.ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *tail.status = (n >> 16) ? EQB_DEV_RANK_EXCEEDS_COUNT : EQB_DEV_OK;
+  }
+  const int e = threadIdx.x;
+  center_block(e < E ? __hip_atomic_load(q + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u, E, tail.b_next);
+}
+
+// Layer form (kTail): `hist` is cleared once summed, the selections read are
+// zeroed (sel_lo is not written: it stays zero), and layer_tail follows.
+template <bool kLocal, bool kTail = false>
 __global__ __launch_bounds__(kNBins) void select_fine_kernel(
-    int32_t* __restrict__ hist, int P, int E, const PartTable pt, const int32_t* __restrict__ sel_hi,
-    const int64_t* __restrict__ rank_in_bin, int32_t* __restrict__ sel_lo,
-    uint16_t* __restrict__ q_bf16, int32_t* __restrict__ hist_sum, int32_t* __restrict__ status,
-    bool clear = false) {
+    int32_t* __restrict__ hist, int P, int E, const PartTable pt, int32_t* __restrict__ sel_hi,
+    int64_t* __restrict__ rank_in_bin, int32_t* __restrict__ sel_lo, uint16_t* __restrict__ q_bf16,
+    int32_t* __restrict__ hist_sum, int32_t* __restrict__ status, const LayerTail tail = LayerTail{}) {
   __shared__ int64_t sh[kNBins];
   const int e = blockIdx.x, v = threadIdx.x, p = kLocal ? (int)blockIdx.y : 0;
   const int64_t out = kLocal ? (int64_t)p * E + e : e;
@@ -104,18 +194,35 @@ __global__ __launch_bounds__(kNBins) void select_fine_kernel(
   } else {
     c = slab_sum(hist + (int64_t)e * kNBins + v, P, (int64_t)E * kNBins);
     if (hist_sum) hist_sum[(int64_t)e * kNBins + v] = (int32_t)c;
-    if (clear) slab_clear(hist + (int64_t)e * kNBins + v, P, (int64_t)E * kNBins);
+    if (kTail) slab_clear(hist + (int64_t)e * kNBins + v, P, (int64_t)E * kNBins);
   }
   const int64_t cum = block_inclusive_scan_256(c, sh);
   const bool ok = u >= 0 && u < kNBins && rho >= 1;
+  const bool failed = v == kNBins - 1 && (!ok || cum < rho);
   if (ok && cum >= rho && cum - c < rho) {
-    sel_lo[out] = v;
-    q_bf16[out] = kappa_inv(((uint32_t)u << 8) | (uint32_t)v);
+    const uint16_t bits = kappa_inv(((uint32_t)u << 8) | (uint32_t)v);
+    if (kTail) {
+      store_bhat(q_bf16 + out, bits);
+    } else {
+      sel_lo[out] = v;
+      q_bf16[out] = bits;
+    }
   }
-  if (v == kNBins - 1 && (!ok || cum < rho)) {
-    sel_lo[out] = -1;
-    q_bf16[out] = 0x7FC0;
-    if (status) *status = EQB_DEV_RANK_EXCEEDS_COUNT;
+  if (failed) {
+    if (kTail) {
+      store_bhat(q_bf16 + out, 0x7FC0);
+    } else {
+      sel_lo[out] = -1;
+      q_bf16[out] = 0x7FC0;
+      if (status) *status = EQB_DEV_RANK_EXCEEDS_COUNT;
+    }
+  }
+  if (kTail) {
+    if (v == 0) {                  // every thread read them before the scan's barrier
+      sel_hi[out] = 0;
+      rank_in_bin[out] = 0;
+    }
+    layer_tail(tail, failed, q_bf16, E);
   }
 }
 
@@ -131,9 +238,9 @@ __global__ __launch_bounds__(kNBins) void select_fine_kernel(
 // below 2^16 and the sums below 2^31 (T < 2^31).
 constexpr int kPartThreads = 512;
 __global__ __launch_bounds__(kPartThreads) void select_fine_parts_kernel(
-    const uint32_t* __restrict__ part, int nparts, int E, const int32_t* __restrict__ sel_hi,
-    const int64_t* __restrict__ rank_in_bin, int32_t* __restrict__ sel_lo, uint16_t* __restrict__ q_bf16,
-    int32_t* __restrict__ hist_sum) {
+    const uint32_t* __restrict__ part, int nparts, int E, int32_t* __restrict__ sel_hi,
+    int64_t* __restrict__ rank_in_bin, uint16_t* __restrict__ q_bf16, int32_t* __restrict__ hist_sum,
+    const LayerTail tail) {
   constexpr int kW = kPartThreads / 64;
   __shared__ uint32_t sh[kW][2 * kNBins];   // per wave: raw bins of expert 2m, then of 2m+1
   __shared__ int sh_tot[kW];
@@ -196,57 +303,22 @@ __global__ __launch_bounds__(kPartThreads) void select_fine_parts_kernel(
   __syncthreads();
   for (int w = 4 * x; w < wave; ++w) y += sh_tot[w];
   const int64_t cum = y;
-  if (ok && cum >= rho && cum - c < rho) {
-    sel_lo[e] = v;
-    q_bf16[e] = kappa_inv(((uint32_t)u << 8) | (uint32_t)v);
+  const bool failed = v == kNBins - 1 && (!ok || cum < rho);
+  if (ok && cum >= rho && cum - c < rho) store_bhat(q_bf16 + e, kappa_inv(((uint32_t)u << 8) | (uint32_t)v));
+  if (failed) store_bhat(q_bf16 + e, 0x7FC0);
+  if (v == 0) {                    // every thread read them before the scan's barrier
+    sel_hi[e] = 0;
+    rank_in_bin[e] = 0;
   }
-  if (v == kNBins - 1 && (!ok || cum < rho)) {
-    sel_lo[e] = -1;
-    q_bf16[e] = 0x7FC0;
-  }
-}
-
-// b = b_hat - mean(b_hat): binary64 sum in ascending expert order, divided by
-// E, difference in binary64, one rounding to binary32.  With status_out (the
-// layer form) the kernel also writes the layer's status (an expert whose fine
-// selection failed, sel_lo = -1, holds fewer counts than its rank) and, as the
-// layer's last kernel, zeroes the selections it leaves behind in the
-// workspace (sel_hi, rank_in_bin, sel_lo), each by the thread that read it.
-__global__ __launch_bounds__(256) void center_kernel(const uint16_t* __restrict__ q, int E,
-                                                     float* __restrict__ b_next,
-                                                     int32_t* __restrict__ sel_lo = nullptr,
-                                                     int32_t* __restrict__ status_out = nullptr,
-                                                     int32_t* __restrict__ sel_hi = nullptr,
-                                                     int64_t* __restrict__ rank_in_bin = nullptr) {
-  __shared__ double val[256];
-  __shared__ double mean;
-  for (int e = threadIdx.x; e < E; e += blockDim.x) val[e] = (double)__uint_as_float((uint32_t)q[e] << 16);
-  int bad = 0;
-  if (status_out) {
-    for (int e = threadIdx.x; e < E; e += blockDim.x) {
-      bad |= (int)(sel_lo[e] < 0);
-      sel_lo[e] = 0;
-      sel_hi[e] = 0;
-      rank_in_bin[e] = 0;
-    }
-  }
-  bad = __syncthreads_or(bad);
-  if (threadIdx.x == 0) {
-    double acc = 0.0;
-    for (int e = 0; e < E; ++e) acc += val[e];
-    mean = acc / (double)E;
-    if (status_out) *status_out = bad ? EQB_DEV_RANK_EXCEEDS_COUNT : EQB_DEV_OK;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < E; e += blockDim.x) b_next[e] = (float)(val[e] - mean);
+  layer_tail(tail, failed, q_bf16, E);
 }
 
 // The layer's selections: the counts sit in P * nsub slabs, all summed; the
 // loads in P rows.
 eqb_status launch_layer_selects(int pass, int32_t* hist, int P, int nsub, int E, int64_t r, int32_t* sel_hi,
-                                int64_t* rank_in_bin, int32_t* sel_lo, uint16_t* q_bf16, float* b_next,
+                                int64_t* rank_in_bin, uint16_t* q_bf16, float* b_next,
                                 int32_t* hist_sum, int32_t* load_acc, int32_t* load_out, int32_t* status,
-                                hipStream_t s, bool slab16) {
+                                int32_t* ticket, hipStream_t s, bool slab16) {
   PartTable none{};
   none.P = P;
   const int nslabs = P * nsub;
@@ -259,20 +331,16 @@ eqb_status launch_layer_selects(int pass, int32_t* hist, int P, int nsub, int E,
                                                        nullptr, true, load_acc, load_out);
     return launch_status();
   }
-  select_fine_kernel<false><<<E, kNBins, 0, s>>>(hist, nslabs, E, none, sel_hi, rank_in_bin, sel_lo, q_bf16,
-                                                 hist_sum, nullptr, true);
-  if (launch_status() != EQB_OK) return EQB_ERR_HIP;
-  center_kernel<<<1, 256, 0, s>>>(q_bf16, E, b_next, sel_lo, status, sel_hi, rank_in_bin);
+  select_fine_kernel<false, true><<<E, kNBins, 0, s>>>(hist, nslabs, E, none, sel_hi, rank_in_bin, nullptr, q_bf16,
+                                                       hist_sum, nullptr, LayerTail{ticket, b_next, status});
   return launch_status();
 }
 
 eqb_status launch_layer_select_parts(const uint32_t* part, int nparts, int E, int32_t* sel_hi,
-                                     int64_t* rank_in_bin, int32_t* sel_lo, uint16_t* q_bf16, float* b_next,
-                                     int32_t* hist_sum, int32_t* status, hipStream_t s) {
-  select_fine_parts_kernel<<<E / 2, kPartThreads, 0, s>>>(part, nparts, E, sel_hi, rank_in_bin, sel_lo, q_bf16,
-                                                          hist_sum);
-  if (launch_status() != EQB_OK) return EQB_ERR_HIP;
-  center_kernel<<<1, 256, 0, s>>>(q_bf16, E, b_next, sel_lo, status, sel_hi, rank_in_bin);
+                                     int64_t* rank_in_bin, uint16_t* q_bf16, float* b_next,
+                                     int32_t* hist_sum, int32_t* status, int32_t* ticket, hipStream_t s) {
+  select_fine_parts_kernel<<<E / 2, kPartThreads, 0, s>>>(part, nparts, E, sel_hi, rank_in_bin, q_bf16, hist_sum,
+                                                          LayerTail{ticket, b_next, status});
   return launch_status();
 }
 
@@ -296,8 +364,8 @@ eqb_status launch_layer(const RouteArgs& route, int64_t r, const LayerWorkspace&
   if (st != EQB_OK) return st;
   if ((st = mark(marks, 1, s)) != EQB_OK) return st;
   const int P = a.pt.P, E = a.E;
-  st = launch_layer_selects(1, w.hist_hi, P, w.nsub, E, r, w.sel_hi, w.rank_in_bin, nullptr, nullptr, nullptr,
-                            hist_hi_sum, w.load_acc, load_out, nullptr, s, slab16);
+  st = launch_layer_selects(1, w.hist_hi, P, w.nsub, E, r, w.sel_hi, w.rank_in_bin, nullptr, nullptr,
+                            hist_hi_sum, w.load_acc, load_out, nullptr, nullptr, s, slab16);
   if (st != EQB_OK) return st;
   if ((st = mark(marks, 2, s)) != EQB_OK) return st;
   MarginArgs m;
@@ -315,11 +383,11 @@ eqb_status launch_layer(const RouteArgs& route, int64_t r, const LayerWorkspace&
   if (st != EQB_OK) return st;
   if ((st = mark(marks, 3, s)) != EQB_OK) return st;
   if (nparts > 0)
-    st = launch_layer_select_parts(w.part, nparts, E, w.sel_hi, w.rank_in_bin, w.sel_lo, q_bf16, b_next,
-                                   hist_lo_sum, dev_status, s);
+    st = launch_layer_select_parts(w.part, nparts, E, w.sel_hi, w.rank_in_bin, q_bf16, b_next,
+                                   hist_lo_sum, dev_status, w.tickets, s);
   else
-    st = launch_layer_selects(2, w.hist_lo, P, w.nsub, E, r, w.sel_hi, w.rank_in_bin, w.sel_lo, q_bf16, b_next,
-                              hist_lo_sum, nullptr, nullptr, dev_status, s);
+    st = launch_layer_selects(2, w.hist_lo, P, w.nsub, E, r, w.sel_hi, w.rank_in_bin, q_bf16, b_next,
+                              hist_lo_sum, nullptr, nullptr, dev_status, w.tickets, s);
   if (st != EQB_OK) return st;
   return mark(marks, 4, s);
 }
