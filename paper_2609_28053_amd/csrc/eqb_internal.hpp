@@ -43,11 +43,12 @@ struct MarginArgs {
 // (2m, 2m+1), 256 words holding the two experts' 16-bit counts of raw low
 // byte j in their low and high halves.
 __host__ __device__ inline int64_t part_words(int E) { return (int64_t)(E / 2) * kNBins; }
-// Blocks of the fine pass per compute unit (its LDS counts take (E/2) * 257
-// words per block) when it adds its counts to slabs, and the per-block images
-// a layer workspace holds: the image-storing pass runs one block per compute
-// unit, and the workspace has room for one full grid on a device of up to
-// 256 compute units (a larger device runs the pass with fewer, longer blocks).
+// Blocks of the coarse pass per compute unit (its LDS counts take (E/2) * 257
+// words per block), and the images of all E experts a layer workspace holds:
+// the image-storing pass runs at most one block per compute unit, and the
+// workspace has room for one full grid of whole-row blocks on a device of up
+// to 256 compute units (a larger device runs the pass with fewer, longer
+// blocks; blocks of fewer experts store smaller images).
 inline int margin_blocks_per_cu(int E) { return (E / 2) * kHistStride * 4 * 2 <= 160 * 1024 ? 2 : 1; }
 constexpr int kPartCUs = 256;
 inline int layer_part_blocks(int) { return kPartCUs; }
@@ -184,22 +185,23 @@ int num_cus();
 // (0: none).
 int max_blocks_cap();
 
-// Blocks and rows per block for a streaming kernel over T rows that advances
-// rows_per_step rows per block step: at most blocks_per_cu blocks per CU,
-// each owning a contiguous range of ceil(T / blocks) rows (the last may be
-// shorter), and at least min_steps steps per block where T allows (a
-// block's fixed costs, zeroing and flushing its LDS counts, then pay for
-// more rows).  The ranges are not rounded to whole steps: with P equal
-// partitions and a block count that P divides, every partition boundary
-// then falls on a block boundary, and no block pays for a second segment
-// (a second flush and a cold restart of its prefetch).
-inline void grid_for(int64_t T, int rows_per_step, int blocks_per_cu, int* blocks, int64_t* rows_per_block,
-                     int min_steps = 1) {
+// Blocks and rows per block for a streaming kernel over T rows: at most
+// blocks_per_cu blocks per CU, each owning a contiguous range of
+// ceil(T / blocks) rows (the last may be shorter), and at least min_rows rows
+// per block where T allows (a block's fixed costs, zeroing and flushing its
+// LDS counts, then pay for more rows).  With slices > 1 every row range is
+// shared by that many blocks, and *blocks counts the ranges.  The ranges are
+// not rounded to whole steps: with P equal partitions and a block count that P
+// divides, every partition boundary then falls on a block boundary, and no
+// block pays for a second segment (a second flush and a cold restart of its
+// prefetch).
+inline void grid_for(int64_t T, int64_t min_rows, int blocks_per_cu, int* blocks, int64_t* rows_per_block,
+                     int slices = 1) {
   int64_t max_blocks = (int64_t)num_cus() * blocks_per_cu;
   const int cap = max_blocks_cap();
   if (cap > 0 && cap < max_blocks) max_blocks = cap;
-  const int64_t steps = (T + rows_per_step - 1) / rows_per_step;
-  const int64_t want = (steps + min_steps - 1) / min_steps;
+  max_blocks /= slices;
+  const int64_t want = (T + min_rows - 1) / min_rows;
   int64_t nb = want < max_blocks ? want : max_blocks;
   if (nb < 1) nb = 1;
   *rows_per_block = T > 0 ? (T + nb - 1) / nb : 1;

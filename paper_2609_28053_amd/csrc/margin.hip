@@ -15,7 +15,6 @@
 namespace eqb {
 
 constexpr int kMarginU = 3;   // rows per lane per block step
-constexpr int kPartMinRows = 512;    // least rows per block when the blocks store count images
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Counts the margins of one row piece: eight experts e0 .. e0+7 (four packed
@@ -47,34 +46,39 @@ __device__ __forceinline__ void count_piece(uint32_t* sh, const uint4& w, float 
 // sel_stride = 0: every partition uses the selection sel_hi[e] (EQB: the
 // bins chosen from the summed counts).  sel_stride = E: partition p uses its
 // own selection sel_hi[p*E + e] (each shard's own quantile).
+// A block counts C of the E experts (slice b % (E / C) of row group b / (E / C):
+// the slices of a row group run side by side, and their images lie next to
+// each other, as one image of all E experts).
 // part (fine pass with sel_stride 0, at most kSegMax rows per block): the
 // block's counts, summed over the partitions it covers, are stored as one
-// image of part_words(E) words at part + blockIdx.x * part_words(E) (plain
+// image of part_words(C) words at part + blockIdx.x * part_words(C) (plain
 // stores; the fine selection sums the images) instead of being added to the
 // partition slabs, whose atomics queue in the memory system when every block
 // flushes at once.
-template <int E, bool kFine>
+template <int E, int C, bool kFine>
 __global__ __launch_bounds__(kBlock) void margin_hist_kernel(
     const uint16_t* __restrict__ z, const float* __restrict__ tau, int64_t T,
     const int32_t* __restrict__ sel_hi, int sel_stride, int32_t* __restrict__ hist, const PartTable pt,
-    int64_t rows_per_block, uint32_t* __restrict__ part) {
-  constexpr int G = E / 8;
+    int64_t rows_per_group, uint32_t* __restrict__ part) {
+  constexpr int S = E / C;              // slices: block b counts slice b % S of row group b / S
+  constexpr int G = C / 8;
   constexpr int R = 64 / G;
   constexpr int ROWS = kWaves * R * kMarginU;
-  __shared__ __align__(16) uint32_t sh_hist[hist_words<E>()];
-  __shared__ int32_t sh_sel[kFine ? E : 1];   // the segment's selections, for the flush
+  __shared__ __align__(16) uint32_t sh_hist[hist_words<C>()];
+  __shared__ int32_t sh_sel[kFine ? C : 1];   // the segment's selections, for the flush
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane % G, rr = lane / G;
-  const int e0 = g * 8;
-  const uint32_t row0 = hist_row(e0);
-  for (int w = threadIdx.x; w < hist_words<E>() / 4; w += kBlock)
+  const int slice = (int)(blockIdx.x % S), c0 = slice * C;   // the slice's first expert
+  const int e0 = c0 + g * 8;
+  const uint32_t row0 = hist_row(g * 8);
+  for (int w = threadIdx.x; w < hist_words<C>() / 4; w += kBlock)
     reinterpret_cast<uint4*>(sh_hist)[w] = make_uint4(0, 0, 0, 0);
-  for (int w = (hist_words<E>() / 4) * 4 + threadIdx.x; w < hist_words<E>(); w += kBlock) sh_hist[w] = 0;
+  for (int w = (hist_words<C>() / 4) * 4 + threadIdx.x; w < hist_words<C>(); w += kBlock) sh_hist[w] = 0;
   __syncthreads();
 
-  int64_t r0, r1;
-  block_rows(T, rows_per_block, &r0, &r1);
+  const int64_t r0 = (int64_t)(blockIdx.x / S) * rows_per_group;
+  const int64_t r1 = r0 + rows_per_group < T ? r0 + rows_per_group : T;
   // Rows are visited last to first: the route sweep that precedes this one
   // reads every block range first to last, so the rows it read last may still
   // be held by the memory-side cache.
@@ -83,7 +87,7 @@ __global__ __launch_bounds__(kBlock) void margin_hist_kernel(
     if (kFine) {
       // read once here: the flush looks a selection up per populated bin,
       // and a global load there would sit on its critical path
-      for (int e = threadIdx.x; e < E; e += kBlock) sh_sel[e] = sel[e];
+      for (int e = threadIdx.x; e < C; e += kBlock) sh_sel[e] = sel[c0 + e];
     }
     uint32_t csel[4];
 #pragma unroll
@@ -135,11 +139,11 @@ __global__ __launch_bounds__(kBlock) void margin_hist_kernel(
     }
     if (kFine && part) return;   // the counts stay in LDS until the block's image is stored
     __syncthreads();
-    int32_t* slab = count_slab(hist, pt, p, E);
+    int32_t* slab = count_slab(hist, pt, p, E) + c0 * kNBins;
     if (!kFine) {
-      flush_hist<E, false>(sh_hist, slab, nullptr);
+      flush_hist<C, false>(sh_hist, slab, nullptr);
     } else {
-      flush_hist<E, true>(sh_hist, slab, sh_sel);
+      flush_hist<C, true>(sh_hist, slab, sh_sel);
     }
     __syncthreads();
   });
@@ -147,40 +151,81 @@ __global__ __launch_bounds__(kBlock) void margin_hist_kernel(
     __syncthreads();
     // four words of one pair's row per thread: word m*257 + 4k.. in LDS,
     // 16 bytes at m*256 + 4k in the image
-    uint4* dst = reinterpret_cast<uint4*>(part + (int64_t)blockIdx.x * part_words(E));
-    for (int it = threadIdx.x; it < (E / 2) * (kNBins / 4); it += kBlock) {
+    uint4* dst = reinterpret_cast<uint4*>(part + (int64_t)blockIdx.x * part_words(C));
+    for (int it = threadIdx.x; it < (C / 2) * (kNBins / 4); it += kBlock) {
       const uint32_t* src = sh_hist + (it / (kNBins / 4)) * kHistStride + 4 * (it % (kNBins / 4));
       dst[it] = make_uint4(src[0], src[1], src[2], src[3]);
     }
   }
 }
 
+// Blocks: at most one per CU (two fit where the LDS counts are small, but each
+// pays for its own zeroing and its own counts to hand over: a slab pass of
+// 600,000 tokens, E = 128 took 127 us with its layer at one per CU and 148 at
+// two), and at least min_rows rows per block.
+template <int E, int C>
+eqb_status launch_fine(const MarginArgs& a, int min_rows, hipStream_t s, int* part_used) {
+  static_assert(hist_words<C>() == (C / 2) * kHistStride, "LDS counts as part_words assumes");
+  constexpr int S = E / C;
+  int groups;
+  int64_t rpg;
+  grid_for(a.T, min_rows, 1, &groups, &rpg, S);
+  const bool use_part = a.part != nullptr && a.sel_stride == 0 && groups <= a.part_blocks && rpg <= kSegMax;
+  if (part_used) *part_used = use_part ? groups : 0;
+  margin_hist_kernel<E, C, true><<<groups * S, kBlock, 0, s>>>(a.z, a.tau, a.T, a.sel_hi, a.sel_stride, a.hist, a.pt,
+                                                              rpg, use_part ? a.part : nullptr);
+  return launch_status();
+}
+
+// Experts per block of the fine pass.  A block of C experts hands over C * 256
+// counts (an image, or atomics on a slab) whatever its rows: narrow blocks over
+// more rows hand over less in all, but read a row in pieces of 2C bytes, which
+// costs bandwidth once the batch comes from HBM.  Measured, layer in us by C:
+//   images, E = 256:  8,192 tokens 33.7 (32), 35.0 (64), 39.4 (256)
+//                    32,768 tokens 42.3 (32), 41.2 (64), 45.5 (256)
+//                   300,000 tokens 118 (32), 95 (64), 99 (256)
+//                   600,000 tokens 205 (32), 162 (64), 163 (256)
+//                 4,194,304 tokens 901 (64), 874 (128), 868 (256)
+//   images, E = 64:  60,000 tokens 33.0 (32), 34.6 (64); 262,144 46.7 (32), 44.2 (64)
+//   slabs, E = 256: 300,000 tokens 124 (32), 105 (64), 143 (256)
+//                 1,200,000 tokens 369 (32), 285 (64), 286 (128), 312 (256)
+//                 2,000,000 tokens 457 (64), 450 (128), 467 (256); 4,194,304 901, 878, 883
+//   slabs, E = 64:  262,144 tokens 55.6 (32), 59.3 (64); 1,000,000 108 (32), 102 (64)
+// so the lines are drawn by the logits of the batch.
+inline int fine_width(int E, int64_t T, bool part) {
+  const int64_t n = T * E;
+  int c;
+  if (part) c = n <= (1ll << 22) ? 32 : n <= (1ll << 27) ? 64 : E;
+  else c = n <= (1ll << 24) ? 32 : n <= (1ll << 28) ? 64 : 128;
+  c = c < E ? c : E;
+  // a grid cap below one block per slice: whole rows
+  const int cap = max_blocks_cap();
+  return cap > 0 && cap < E / c ? E : c;
+}
+
 template <int E>
 eqb_status launch_margin_e(bool fine, const MarginArgs& a, hipStream_t s, int* part_used) {
-  static_assert(hist_words<E>() == (E / 2) * kHistStride, "LDS counts as margin_blocks_per_cu assumes");
-  int blocks;
-  int64_t rpb;
-  const int rows_per_step = kWaves * (64 / (E / 8)) * kMarginU;
-  // At least 1,024 rows per block when the counts are flushed with atomics:
-  // at one rank's share of the paper's batch (147,456 tokens, E = 256) that
-  // roughly halves the blocks whose LDS counts are zeroed and flushed; large
-  // batches still fill every CU.  Per-block images cost a block far less, so
-  // their blocks may be shorter; they run one block per CU (half the images
-  // for the selection to sum where two would fit, and a faster pass: E = 64
-  // and 128 layers took 7-13% less time per step).
-  const bool want_part = fine && a.part != nullptr && a.sel_stride == 0;
-  const int min_rows = want_part ? kPartMinRows : 1024;
-  grid_for(a.T, rows_per_step, want_part ? 1 : margin_blocks_per_cu(E), &blocks, &rpb,
-           (min_rows + rows_per_step - 1) / rows_per_step);
-  const bool use_part = want_part && blocks <= a.part_blocks && rpb <= kSegMax;
-  if (part_used) *part_used = use_part ? blocks : 0;
-  if (fine)
-    margin_hist_kernel<E, true><<<blocks, kBlock, 0, s>>>(a.z, a.tau, a.T, a.sel_hi, a.sel_stride, a.hist,
-                                                         a.pt, rpb, use_part ? a.part : nullptr);
-  else
-    margin_hist_kernel<E, false><<<blocks, kBlock, 0, s>>>(a.z, a.tau, a.T, a.sel_hi, 0, a.hist, a.pt, rpb,
-                                                          nullptr);
-  return launch_status();
+  if (part_used) *part_used = 0;
+  if (!fine) {
+    const int rows_per_step = kWaves * (64 / (E / 8)) * kMarginU;
+    int blocks;
+    int64_t rpb;
+    // at least 1,024 rows per block: half the blocks whose LDS counts are
+    // zeroed and flushed on a small batch
+    grid_for(a.T, ((1024 + rows_per_step - 1) / rows_per_step) * rows_per_step, margin_blocks_per_cu(E), &blocks,
+             &rpb);
+    margin_hist_kernel<E, E, false><<<blocks, kBlock, 0, s>>>(a.z, a.tau, a.T, a.sel_hi, 0, a.hist, a.pt, rpb,
+                                                              nullptr);
+    return launch_status();
+  }
+  const bool part = a.part != nullptr && a.sel_stride == 0;
+  const int c = fine_width(E, a.T, part);
+  // images cost a block little, slabs (atomics) more
+  const int min_rows = !part ? 1024 : c < E ? 256 : 512;
+  if constexpr (E > 32) if (c == 32) return launch_fine<E, 32>(a, min_rows, s, part_used);
+  if constexpr (E > 64) if (c == 64) return launch_fine<E, 64>(a, min_rows, s, part_used);
+  if constexpr (E > 128) if (c == 128) return launch_fine<E, 128>(a, min_rows, s, part_used);
+  return launch_fine<E, E>(a, min_rows, s, part_used);
 }
 
 eqb_status launch_margin(bool fine, const MarginArgs& a, hipStream_t s, int* part_used) {
