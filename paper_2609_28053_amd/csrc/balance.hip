@@ -139,58 +139,88 @@ __global__ __launch_bounds__(kBlock) void lei_inject_kernel(
 
 // ------------------------------------- router backward with LEI ---------
 // grad_z[t,e] = (g[t,e] + inj[p(t),e]) * sigmoid'(z[t,e]), where g[t,e] is
-// grad_score[t,k] for e = topk_idx[t,k] and 0 for the other experts.  G = E/8
-// lanes hold a row, 8 experts each (one 16-byte load of z, two of grad_z),
-// and every lane works on kBwdU rows per step.  The K mixture gradients of a
-// row are scattered into a per-wave LDS row (zeroed first) and read back 8 at
-// a time.  With K <= G lane g of a row owns pair k = g, and the next step's
-// logits and pairs are loaded while a step is processed; a larger K reads its
-// pairs inside the step.
-constexpr int kBwdU = 2;
+// grad_score[t,k] for e = topk_idx[t,k] and 0 for the other experts.  G = E/4
+// lanes hold a row, 4 experts each, and every lane works on kBwdU rows per
+// step: each load of z, store of grad_z and LDS read of a wave is then of
+// consecutive bytes (512, 1,024 and 1,024) at every E.  The K mixture gradients
+// of a row are scattered into a per-wave LDS row of zeros, read back 4 at a time,
+// and their places zeroed again.  With K <= G lane g of a row owns pair k = g,
+// and the next step's logits and pairs are loaded while a step is processed; a
+// larger K reads its pairs inside the step.
+//
+// Bound by memory: 2E + 8K bytes read and 4E written per row.  The kernel took
+// 86 VGPRs, so that only one of the two 1,024-thread blocks per CU of its grid
+// ran at a time, and about 30 instructions per logit for sigmoid'.  Offsets of
+// 32 bits from the segment's bases bring it under 64 VGPRs, eight waves per
+// SIMD, in blocks of 512 threads.  Non-temporal loads and stores (a pass reads
+// and writes each byte once) pay once both are of whole lines.  With the
+// residual's launch, before -> after: E = 256, 147,456 rows 63.7 -> 48.4 us;
+// E = 128, 1,000,003 rows, K = 8 191 -> 157 (5.3 TB/s); E = 64, 300,001 rows,
+// K = 16 53.7 -> 29.7; E = 16, 4,000,001 rows 108 -> 88.  Four rows per step
+// spill at 64 VGPRs (168 us at E = 128), two take 159; six waves per SIMD 175;
+// plain stores 172 to 182.
+constexpr int kBwdU = 3;
+constexpr int kBwdBlock = 512, kBwdWaves = kBwdBlock / 64;
+constexpr int kBwdBlocksPerCu = 2048 / kBwdBlock;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-template <int E>
-__global__ __launch_bounds__(kBlock) void lei_router_backward_kernel(
+template <int E, bool kOnePair>
+__global__ __launch_bounds__(kBwdBlock, 8) void lei_router_backward_kernel(
     const uint16_t* __restrict__ z, const int32_t* __restrict__ topk_idx, const float* __restrict__ grad_score,
     const float* __restrict__ inj, int64_t T, int K, float* __restrict__ grad_z, const PartTable pt,
     int64_t rows_per_block) {
-  constexpr int G = E / 8;
+  constexpr int G = E / 4;
   constexpr int R = 64 / G;
-  constexpr int ROWS = kWaves * R * kBwdU;
-  __shared__ __align__(16) float sh_g[kWaves][kBwdU][R][E];
+  constexpr uint32_t ROWS = kBwdWaves * R * kBwdU;
+  __shared__ __align__(16) float sh_g[kBwdWaves][kBwdU][R][E];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane % G, rr = lane / G;
-  const int e0 = g * 8;
-  const bool one_pair = K <= G;
+  float* my = &sh_g[wave][0][rr][0];      // row u of this lane: my + u * R * E
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  auto place = [&](int u) -> f32x4& { return *reinterpret_cast<f32x4*>(my + u * R * E + 4 * g); };
+#pragma unroll
+  for (int u = 0; u < kBwdU; ++u) place(u) = zero;
+  lds_wave_sync();
   int64_t r0, r1;
   block_rows(T, rows_per_block, &r0, &r1);
   for_each_segment(r0, r1, pt, [&](int p, int64_t s0, int64_t s1) {
-    float d[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) d[j] = inj ? inj[(int64_t)p * E + e0 + j] : 0.0f;
-    auto row_of = [&](int64_t base, int u) -> int64_t { return base + (int64_t)(u * kWaves + wave) * R + rr; };
+    // a segment holds at most kSegMax rows: 32-bit byte offsets from its bases
+    const int64_t su = wave_uniform(s0);
+    const uint16_t* seg_z = z + su * E;
+    const int32_t* seg_idx = topk_idx + su * K;
+    const float* seg_gs = grad_score + su * K;
+    float* seg_gz = grad_z + su * E;
+    const uint32_t n = (uint32_t)(s1 - s0);
+    f32x4 d = zero;
+    if (inj) {
+      const float* di = inj + (int64_t)p * E + 4 * g;
+      d = f32x4{di[0], di[1], di[2], di[3]};
+    }
+    auto row_of = [&](uint32_t base, int u) -> uint32_t { return base + (uint32_t)((wave * kBwdU + u) * R + rr); };
     // logits and this lane's pair of its rows at step base
-    auto load = [&](int64_t base, uint4 (&zw)[kBwdU], int (&e)[kBwdU], float (&gv)[kBwdU]) {
+    auto load = [&](uint32_t base, u32x2 (&zw)[kBwdU], int (&e)[kBwdU], float (&gv)[kBwdU]) {
 #pragma unroll
       for (int u = 0; u < kBwdU; ++u) {
-        const int64_t t = row_of(base, u);
-        zw[u] = make_uint4(0, 0, 0, 0);
+        const uint32_t t = row_of(base, u);
+        zw[u] = u32x2{0, 0};
         e[u] = -1;
         gv[u] = 0.0f;
-        if (t < s1) {
-          zw[u] = *reinterpret_cast<const uint4*>(z + t * E + e0);
-          if (one_pair && g < K) {
-            e[u] = topk_idx[t * K + g];
-            gv[u] = grad_score[t * K + g];
+        if (t < n) {
+          zw[u] = __builtin_nontemporal_load(&at<const u32x2>(seg_z, (t * E + 4 * g) * 2u));
+          if (kOnePair && g < K) {
+            e[u] = at<const int32_t>(seg_idx, (t * K + g) * 4u);
+            gv[u] = at<const float>(seg_gs, (t * K + g) * 4u);
           }
         }
       }
     };
-    uint4 zn[kBwdU];
+    u32x2 zn[kBwdU];
     int en[kBwdU];
     float gn[kBwdU];
-    load(s0, zn, en, gn);
-    for (int64_t base = s0; base < s1; base += ROWS) {
-      uint4 zw[kBwdU];
+    load(0, zn, en, gn);
+    for (uint32_t base = 0; base < n; base += ROWS) {
+      u32x2 zw[kBwdU];
       int ec[kBwdU];
       float gc[kBwdU];
 #pragma unroll
@@ -199,51 +229,53 @@ __global__ __launch_bounds__(kBlock) void lei_router_backward_kernel(
         ec[u] = en[u];
         gc[u] = gn[u];
       }
-      if (base + ROWS < s1) load(base + ROWS, zn, en, gn);
+      if (base + ROWS < n) load(base + ROWS, zn, en, gn);
       // scatter the rows' mixture gradients
 #pragma unroll
       for (int u = 0; u < kBwdU; ++u) {
-        float* myrow = sh_g[wave][u][rr];
-        *reinterpret_cast<float4*>(myrow + e0) = make_float4(0.f, 0.f, 0.f, 0.f);
-        *reinterpret_cast<float4*>(myrow + e0 + 4) = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-      lds_wave_sync();
-#pragma unroll
-      for (int u = 0; u < kBwdU; ++u) {
-        const int64_t t = row_of(base, u);
-        float* myrow = sh_g[wave][u][rr];
-        if (t < s1) {
-          if (one_pair) {
-            if (ec[u] >= 0 && ec[u] < E) myrow[ec[u]] = gc[u];
-          } else {
-            for (int k = g; k < K; k += G) {
-              const int e = topk_idx[t * K + k];
-              if (e >= 0 && e < E) myrow[e] = grad_score[t * K + k];
-            }
+        const uint32_t t = row_of(base, u);
+        if (kOnePair) {
+          if (ec[u] >= 0 && ec[u] < E) my[u * R * E + ec[u]] = gc[u];
+        } else if (t < n) {
+          for (int k = g; k < K; k += G) {
+            const int e = at<const int32_t>(seg_idx, (t * K + k) * 4u);
+            if (e >= 0 && e < E) my[u * R * E + e] = at<const float>(seg_gs, (t * K + k) * 4u);
           }
         }
       }
       lds_wave_sync();
+      float zmax = 0.0f;
 #pragma unroll
       for (int u = 0; u < kBwdU; ++u) {
-        const int64_t t = row_of(base, u);
-        const float* myrow = sh_g[wave][u][rr];
-        const float4 ga = *reinterpret_cast<const float4*>(myrow + e0);
-        const float4 gb = *reinterpret_cast<const float4*>(myrow + e0 + 4);
-        const float gm[8] = {ga.x, ga.y, ga.z, ga.w, gb.x, gb.y, gb.z, gb.w};
-        const uint32_t w4[4] = {zw[u].x, zw[u].y, zw[u].z, zw[u].w};
-        float o[8];
+        const uint32_t t = row_of(base, u);
+        const f32x4 gm = place(u);
+        const float zf[4] = {bf16_lo(zw[u].x), bf16_hi(zw[u].x), bf16_lo(zw[u].y), bf16_hi(zw[u].y)};
+        f32x4 o;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float zf = (j & 1) ? bf16_hi(w4[j >> 1]) : bf16_lo(w4[j >> 1]);
-          o[j] = (gm[j] + d[j]) * sigmoid_prime_fast(zf);
-        }
-        if (t < s1) {
-          *reinterpret_cast<float4*>(grad_z + t * E + e0) = make_float4(o[0], o[1], o[2], o[3]);
-          *reinterpret_cast<float4*>(grad_z + t * E + e0 + 4) = make_float4(o[4], o[5], o[6], o[7]);
+        for (int j = 0; j < 4; ++j) o[j] = (gm[j] + d[j]) * sigmoid_prime_bf16(zf[j]);
+        zmax = max3_abs(max3_abs(zmax, zf[0], zf[1]), zf[2], zf[3]);
+        if (t < n) __builtin_nontemporal_store(o, &at<f32x4>(seg_gz, (t * E + 4 * g) * 4u));
+      }
+      // logits of 32 or more (rare): the lane computes those again, one by one
+      if (__builtin_expect(__any(!(zmax < kSigmoidPrimeMax)), 0)) {
+#pragma unroll 1
+        for (int i = 0; i < kBwdU * 4; ++i) {
+          const int u = i >> 2, e = 4 * g + (i & 3);
+          const uint32_t t = row_of(base, u);
+          if (t >= n) continue;
+          const float zf = bf16_lo(seg_z[t * E + e]);
+          if (fabsf(zf) < kSigmoidPrimeMax) continue;
+          const float di = inj ? inj[(int64_t)p * E + e] : 0.0f;
+          seg_gz[t * E + e] = (my[u * R * E + e] + di) * sigmoid_prime_fast(zf);
         }
       }
-      lds_wave_sync();          // the row buffers are rewritten by the next step
+      if (kOnePair) lds_wave_sync();   // every place has been read
+#pragma unroll
+      for (int u = 0; u < kBwdU; ++u) {
+        if (!kOnePair) place(u) = zero;
+        else if (ec[u] >= 0 && ec[u] < E) my[u * R * E + ec[u]] = 0.0f;
+      }
+      lds_wave_sync();          // the next step scatters into zeros
     }
   });
 }
@@ -253,8 +285,11 @@ static void launch_backward_e(const uint16_t* z, const int32_t* idx, const float
                               int K, float* gz, const PartTable& pt, hipStream_t s) {
   int blocks;
   int64_t rpb;
-  grid_for(T, kWaves * (64 / (E / 8)) * kBwdU, 2, &blocks, &rpb);
-  lei_router_backward_kernel<E><<<blocks, kBlock, 0, s>>>(z, idx, gs, inj, T, K, gz, pt, rpb);
+  grid_for(T, kBwdWaves * (256 / E) * kBwdU, kBwdBlocksPerCu, &blocks, &rpb);
+  if (K <= E / 4)
+    lei_router_backward_kernel<E, true><<<blocks, kBwdBlock, 0, s>>>(z, idx, gs, inj, T, K, gz, pt, rpb);
+  else
+    lei_router_backward_kernel<E, false><<<blocks, kBwdBlock, 0, s>>>(z, idx, gs, inj, T, K, gz, pt, rpb);
 }
 
 eqb_status launch_lei_router_backward(const uint16_t* z, const int32_t* idx, const float* gs, const float* inj,

@@ -81,14 +81,6 @@ __device__ __forceinline__ uint32_t z_from_key(int key, float b, bool* ok) {
   return zc;
 }
 
-// Element at a 32-bit byte offset from a (wave-uniform) base pointer: the
-// form the loads and stores take as a 64-bit scalar base plus a 32-bit
-// vector offset.
-template <class V, class B>
-__device__ __forceinline__ V& at(B* base, uint32_t byte_off) {
-  return *reinterpret_cast<V*>(reinterpret_cast<char*>(const_cast<std::remove_const_t<B>*>(base)) + byte_off);
-}
-
 // Coarse counts of the fast kernel for E >= 64: a slot-major packed
 // histogram.  Experts e, e+1 (e = 4j + 2h, a piece of four experts starting
 // at 4j and its half h) share a word, counted in its low and high 16 bits.
