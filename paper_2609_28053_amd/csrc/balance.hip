@@ -257,14 +257,14 @@ __global__ __launch_bounds__(kBwdBlock, 8) void lei_router_backward_kernel(
         if (t < n) __builtin_nontemporal_store(o, &at<f32x4>(seg_gz, (t * E + 4 * g) * 4u));
       }
       // logits of 32 or more (rare): the lane computes those again, one by one
-      if (__builtin_expect(__any(!(zmax < kSigmoidPrimeMax)), 0)) {
+      if (__builtin_expect(__any(!(zmax < kSigmoidMax)), 0)) {
 #pragma unroll 1
         for (int i = 0; i < kBwdU * 4; ++i) {
           const int u = i >> 2, e = 4 * g + (i & 3);
           const uint32_t t = row_of(base, u);
           if (t >= n) continue;
           const float zf = bf16_lo(seg_z[t * E + e]);
-          if (fabsf(zf) < kSigmoidPrimeMax) continue;
+          if (fabsf(zf) < kSigmoidMax) continue;
           const float di = inj ? inj[(int64_t)p * E + e] : 0.0f;
           seg_gz[t * E + e] = (my[u * R * E + e] + di) * sigmoid_prime_fast(zf);
         }

@@ -67,29 +67,35 @@ __device__ __forceinline__ float sigmoid_f32(float x) {
   return ex / (1.0f + ex);
 }
 
-// sigmoid(x) = 1 / (1 + e) for x >= 0 and e / (1 + e) for x < 0, with
-// e = exp(-|x|) = 2^(-|x| log2 e).  The product |x| log2 e is carried as
-// p_hi + p_lo (log2 e split into two binary32 parts, the rounding error of
-// the leading product recovered with an fma), 2^(-p_hi) comes from the
-// hardware exponential and 2^(-p_lo) ~ 1 - p_lo ln 2 corrects it.  Relative
-// error stays within a few ulp for |x| <= 64; larger |x| use the libm path.
+// exp(-a) of a BF16 a in [0, 32].  log2 e = kHi + kLo with kHi of 16 significant
+// bits: a of 8 bits makes a * kHi exact in binary32, so exp(-a) = 2^(-a kHi) *
+// exp(-a kLo ln 2), the second factor 1 - c to c^2/2 < 1.3e-8.
+constexpr float kSigmoidMax = 32.0f;
+__device__ __forceinline__ float exp_neg_bf16(float a) {
+  const float kHi = 1.44268798828125f;
+  const float kLoLn2 = 4.888495368504664e-06f;
+  const float e1 = __builtin_amdgcn_exp2f(-(a * kHi));
+  return __builtin_fmaf(-e1, a * kLoLn2, e1);
+}
+
+// sigmoid(x) of a BF16 x: 1 / (1 + e) for x >= 0 and e / (1 + e) for x < 0, e =
+// exp(-|x|).  The hardware reciprocal r0 (1 ulp) of d = fl(1 + e) takes one
+// Newton step for 1 + e itself: what d lost, e - (d - 1), is exact (d in [1, 2]).
+// |x| above 32 takes the libm path.
 __device__ __forceinline__ float sigmoid_fast(float x) {
   const float a = fabsf(x);
-  if (a > 64.0f) return sigmoid_f32(x);
-  const float kLog2eHi = 1.44269502162933349609375f;   // binary32 nearest to log2(e)
-  const float kLog2eLo = 1.925963033500011e-08f;       // log2(e) - kLog2eHi
-  const float kLn2 = 0.693147180559945309f;
-  const float p_hi = a * kLog2eHi;
-  const float p_lo = __builtin_fmaf(a, kLog2eLo, __builtin_fmaf(a, kLog2eHi, -p_hi));
-  const float e1 = __builtin_amdgcn_exp2f(-p_hi);
-  const float e = __builtin_fmaf(-e1, p_lo * kLn2, e1);
-  const float r = __builtin_amdgcn_rcpf(1.0f + e);
+  if (a > kSigmoidMax) return sigmoid_f32(x);
+  const float e = exp_neg_bf16(a);
+  const float d = 1.0f + e;
+  const float lost = e - (d - 1.0f);
+  const float r0 = __builtin_amdgcn_rcpf(d);
+  const float r = __builtin_fmaf(__builtin_fmaf(-lost, r0, __builtin_fmaf(-d, r0, 1.0f)), r0, r0);
   return x >= 0.0f ? r : e * r;
 }
 
 // sigmoid'(x) = e / (1 + e)^2 with e = exp(-|x|) (the form that keeps its
 // relative accuracy for large |x|), e from the same split base-2 exponential
-// as sigmoid_fast; a few ulp for |x| <= 64, the libm exponential beyond.
+// of any binary32 x; a few ulp for |x| <= 64, the libm exponential beyond.
 __device__ __forceinline__ float sigmoid_prime_fast(float x) {
   const float a = fabsf(x);
   float e;
@@ -110,23 +116,16 @@ __device__ __forceinline__ float sigmoid_prime_fast(float x) {
 
 // sigmoid'(x) of a BF16 x with |x| < 32, in 12 instructions where the form above
 // takes about 30 (an IEEE division, two products to split x log2 e, a test).
-// log2 e = kHi + kLo with kHi of 16 significant bits: x of 8 bits makes a * kHi
-// exact in binary32, so exp(-a) = 2^(-a kHi) * exp(-a kLo ln 2), the second
-// factor 1 - c to c^2/2 < 1.3e-8.  1 + e lies in [1, 2]: the hardware reciprocal
-// (1 ulp) and one Newton step round like the division but for rare last bits, and
-// with q = sigmoid(-a), q - q^2 in one rounding halves what q carries near 0.
-constexpr float kSigmoidPrimeMax = 32.0f;
+// 1 + e lies in [1, 2]: the hardware reciprocal (1 ulp) and one Newton step round
+// like the division but for rare last bits, and with q = sigmoid(-a), q - q^2 in
+// one rounding halves what q carries near 0.
 __device__ __forceinline__ float max3_abs(float m, float a, float b) {
   float r;
   asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(m), "v"(a), "v"(b));
   return r;
 }
 __device__ __forceinline__ float sigmoid_prime_bf16(float x) {
-  const float kHi = 1.44268798828125f;
-  const float kLoLn2 = 4.888495368504664e-06f;
-  const float a = fabsf(x);
-  const float e1 = __builtin_amdgcn_exp2f(-(a * kHi));
-  const float e = __builtin_fmaf(-e1, a * kLoLn2, e1);
+  const float e = exp_neg_bf16(fabsf(x));
   const float d = 1.0f + e;
   const float r0 = __builtin_amdgcn_rcpf(d);
   const float q = e * __builtin_fmaf(__builtin_fmaf(-d, r0, 1.0f), r0, r0);   // sigmoid(-a) <= 1/2

@@ -31,12 +31,20 @@
 
 namespace eqb {
 
-constexpr int kRmax = 16;              // extracted ranks kept per row
+constexpr int kFastKmax = 16;          // widest fan-out of the fast kernel
+// Ranks kept per row: K + 1 and the run of rank K's top 24 bits.  A longer run
+// sends its row to the exact 64-bit path, 25 us of its wave at K = 14: with room
+// for one rank more than K + 1 such a row came once in about a thousand of
+// random logits, with two once in a million.  At E = 64 (16 rows per wave) the
+// LDS holds 19 ranks next to the counts.
+template <int E, int K> constexpr int rank_room() { return K <= 13 ? 16 : E == 64 ? 19 : 24; }
 // Sorted keys kept per lane: the rounds pop at most K+1 keys of a lane and
 // look at one more, and a lane holds N = E/G keys in all, so min(N, K + 2)
 // never runs dry.  Fewer levels cost less per element (one instruction each);
 // a row whose lane does run dry is done again by the full path, so the depth
-// is the one at which that happens in about 1% of rows of random logits.
+// is the one at which that happens in about 1% of rows of random logits (the
+// layer of 1,000,001 tokens, E = 256: K = 13 equal at 7 and 8, K = 14 294 us at
+// 7, 275 at 8, K = 16 347 and 289).
 // Lanes per row.  A row costs a wave its extraction rounds and outputs once,
 // whatever the lanes it is spread over, so few lanes with more experts each
 // are cheaper per element until their longer lists cost more: four lanes
@@ -47,11 +55,10 @@ template <int E> struct FastCfg { static constexpr int G = E >= 128 ? 8 : E >= 3
 template <int E, int K>
 constexpr int list_depth() {
   constexpr int G = FastCfg<E>::G, N = E / G;
-  constexpr int d = G == 8 ? (K <= 8 ? 5 : K <= 11 ? 6 : 7) : G == 4 ? (K <= 4 ? 5 : K <= 6 ? 6 : K <= 8 ? 7 : 8) : 8;
+  constexpr int d = G == 8 ? (K <= 8 ? 5 : K <= 11 ? 6 : K <= 13 ? 7 : 8) : G == 4 ? (K <= 4 ? 5 : K <= 6 ? 6 : K <= 8 ? 7 : K <= 14 ? 8 : 9) : 8;
   constexpr int m = N < K + 2 ? N : K + 2;
   return d < m ? d : m;
 }
-constexpr int kFastKmax = kRmax - 2;
 // Block of the fast kernel: 12 waves, three per SIMD, so that a wave may hold
 // up to 168 VGPRs (with 16 waves the cap of 128 forces spills).
 constexpr int kRouteBlock = 768;
@@ -192,6 +199,7 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
   constexpr int N = E / G;              // experts per lane
   constexpr int NQ = N / 4;             // 8-byte pieces per lane and row
   constexpr int R = 64 / G;             // rows per wave
+  constexpr int kRmax = rank_room<E, KT>();
   constexpr int RSLOT = (kRmax + G - 1) / G;  // rank slots per lane, staged rows
   constexpr int HSLOT = (KT + G) / G;         // rank slots per lane, ranks 0..K
   constexpr int K = KT;
