@@ -28,14 +28,14 @@ thread_local int t_max_blocks = 0;
 
 int max_blocks_cap() { return t_max_blocks; }
 
-eqb_status launch_route(const RouteArgs& a, hipStream_t s, bool* slab16_used) {
+eqb_status launch_route(const RouteArgs& a, hipStream_t s, RouteForm* form) {
   switch (a.E) {
-    case 8: return launch_route_e<8>(a, s, slab16_used);
-    case 16: return launch_route_e<16>(a, s, slab16_used);
-    case 32: return launch_route_e<32>(a, s, slab16_used);
-    case 64: return launch_route_e<64>(a, s, slab16_used);
-    case 128: return launch_route_e<128>(a, s, slab16_used);
-    case 256: return launch_route_e<256>(a, s, slab16_used);
+    case 8: return launch_route_e<8>(a, s, form);
+    case 16: return launch_route_e<16>(a, s, form);
+    case 32: return launch_route_e<32>(a, s, form);
+    case 64: return launch_route_e<64>(a, s, form);
+    case 128: return launch_route_e<128>(a, s, form);
+    case 256: return launch_route_e<256>(a, s, form);
     default: return EQB_ERR_UNSUPPORTED;
   }
 }

@@ -41,6 +41,26 @@ __device__ __forceinline__ int32_t* count_slab(int32_t* hist, const PartTable& p
   return hist + ((int64_t)p * pt.nsub + sub) * E * kNBins;
 }
 
+// The coarse counts that a route block hands over as an image: for each expert
+// pair (2m, 2m+1) kWinBins words, the raw high bytes kWinLo .. kWinLo + 7 (margins
+// from 2^-11 up to 32) and the same with the sign bit, the two experts' 16-bit
+// counts in a word's halves.
+constexpr int kWinBins = 16;
+constexpr int kWinLo = 0x3A;
+static_assert(kWinLo % 2 == 0, "whole pairs of bins");
+__host__ __device__ constexpr int64_t win_words(int E) { return (int64_t)(E / 2) * kWinBins; }
+__device__ __forceinline__ int win_raw(int b) { return ((b & 8) << 4) | (kWinLo + (b & 7)); }
+// the i-th of the 128 pairs (2j, 2j + 1) of raw bytes that lie outside the window
+__device__ __forceinline__ int outside_pair(int i) {
+  const int half = (kNBins - kWinBins) / 4, j = i % half;
+  return i / half * (kNBins / 4) + (j < kWinLo / 2 ? j : j + kWinBins / 4);
+}
+// place of raw high byte hr in the window, or -1
+__device__ __forceinline__ int win_place(int hr) {
+  const unsigned d = (unsigned)((hr & 0x7F) - kWinLo);
+  return d < 8u ? (int)d | ((hr & 0x80) >> 4) : -1;
+}
+
 // ------------------------------------------------------------ BF16 ------
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }

@@ -19,6 +19,23 @@ struct RouteArgs {
   // The layer: `hist` is workspace slabs that only its own coarse selection
   // reads, so the route kernel may use 16-bit counters (PartTable::slab16).
   bool slab16_ok = false;
+  // The layer: room for win_blocks images (win_words(E) words each) of the blocks'
+  // coarse counts.  Where the grid fits, each block stores its window there and
+  // adds only the counts outside it to `hist`, to slab block % RouteForm::slabs.
+  uint32_t* win = nullptr;
+  int win_blocks = 0;
+};
+
+// Slabs that the counts outside the images' windows are spread over, so that the
+// coarse selection reads and clears two instead of eight (147,456 tokens of E =
+// 256: 59.0 us with two, 59.8 with eight).
+constexpr int kWinSlabs = 2;
+
+// How a route launch left the coarse counts.
+struct RouteForm {
+  bool slab16 = false;   // `hist` holds 16-bit slabs (see PartTable)
+  int images = 0;        // images at RouteArgs::win, their counts not in `hist`
+  int slabs = 0;         // slabs of `hist` that may hold counts, the first ones
 };
 
 struct MarginArgs {
@@ -53,10 +70,9 @@ inline int margin_blocks_per_cu(int E) { return (E / 2) * kHistStride * 4 * 2 <=
 constexpr int kPartCUs = 256;
 inline int layer_part_blocks(int) { return kPartCUs; }
 
-// *slab16_used: the coarse counts went to 16-bit slabs (see PartTable).
-eqb_status launch_route(const RouteArgs& a, hipStream_t s, bool* slab16_used = nullptr);
+eqb_status launch_route(const RouteArgs& a, hipStream_t s, RouteForm* form = nullptr);
 template <int E>
-eqb_status launch_route_e(const RouteArgs& a, hipStream_t s, bool* slab16_used);   // route.hip, one object per E
+eqb_status launch_route_e(const RouteArgs& a, hipStream_t s, RouteForm* form);   // route.hip, one object per E
 // *part_used: the number of per-block images the fine pass wrote (0 when it
 // added its counts to a.hist).
 eqb_status launch_margin(bool fine, const MarginArgs& a, hipStream_t s, int* part_used = nullptr);
@@ -66,11 +82,12 @@ eqb_status launch_select(int pass, const int32_t* hist, int P, int E, int64_t r,
                          int64_t* rank_in_bin, int32_t* sel_lo, uint16_t* q_bf16, float* b_next,
                          int32_t* hist_sum, int32_t* status, hipStream_t s);
 
-// slab16: the pass-1 slabs hold 16-bit counters (PartTable::slab16).
+// form: how the route launch left the pass-1 counts; win its images.
 eqb_status launch_layer_selects(int pass, int32_t* hist, int P, int nsub, int E, int64_t r, int32_t* sel_hi,
                                 int64_t* rank_in_bin, uint16_t* q_bf16, float* b_next,
                                 int32_t* hist_sum, int32_t* load_acc, int32_t* load_out, int32_t* status,
-                                int32_t* ticket, hipStream_t s, bool slab16 = false);
+                                int32_t* ticket, hipStream_t s, RouteForm form = RouteForm{},
+                                const uint32_t* win = nullptr);
 // The fine selection of a layer from the fine pass's per-block images
 // (nparts of them), then the centring and status as launch_layer_selects(2).
 eqb_status launch_layer_select_parts(const uint32_t* part, int nparts, int E, int32_t* sel_hi,
@@ -111,8 +128,8 @@ inline int layer_replicas(int P) { return P >= 8 ? 1 : 8 / P; }
 // the fine pass's per-block count images.  Each piece starts on a 256-byte
 // boundary.  The counters (everything before the images) are zero when a
 // layer starts and zero again when it ends: the selection that reads a
-// counter clears it.  The images are scratch: the fine pass overwrites the
-// ones the fine selection reads.
+// counter clears it.  The images are scratch: the route sweep and after it the
+// fine pass overwrite the ones their selections read.
 struct LayerWorkspace {
   int nsub;               // count slabs per partition
   int32_t* hist_hi;       // [P,nsub,E,256]

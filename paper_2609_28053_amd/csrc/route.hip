@@ -108,14 +108,14 @@ constexpr int fast_hist_words() { return kSlotHist<E> ? 2 * 64 * kNBins : hist_w
 // thread and step.
 template <int E>
 __device__ __forceinline__ void flush_hist_slots(uint32_t* sh, int32_t* __restrict__ slab) {
-  constexpr int kItems = fast_hist_words<E>() / 2;
+  constexpr int kSlots = E / 4, kItems = 2 * (kNBins / 2) * kSlots;
   for (int i = threadIdx.x; i < kItems; i += blockDim.x) {
     const int it = flush_word(i, kItems);
-    const int arr = it >> 13, j = (it >> 6) & 127, slot = it & 63;
+    const int arr = it / (kItems / 2), j = it / kSlots % (kNBins / 2), slot = 64 - kSlots + it % kSlots;
     const int w0 = arr * 16384 + 2 * j * 64 + slot;
     const uint32_t c0 = sh[w0], c1 = sh[w0 + 64];
     if (c0 | c1) {
-      const int e = 4 * (63 - slot) + 2 * arr;   // < E: no other slot is counted
+      const int e = 4 * (63 - slot) + 2 * arr;
       const bool neg = (2 * j) & 0x80;
       const int k0 = kappa_hi_of_raw(2 * j);
       if ((c0 | c1) & 0xFFFFu) add_raw_pair(slab + e * kNBins, neg, c0 & 0xFFFFu, c1 & 0xFFFFu, k0);
@@ -126,6 +126,17 @@ __device__ __forceinline__ void flush_hist_slots(uint32_t* sh, int32_t* __restri
   }
 }
 
+// Adds the words c0, c1 of raw bins r, r + 1 (r even, k0 its kappa bin, neg: r of
+// negative margins) of expert pair m to a slab of 16-bit counters: four adjacent
+// ones, one 64-bit atomic.
+__device__ __forceinline__ void add_words16(int32_t* __restrict__ slab32, int m, bool neg, int k0, uint32_t c0,
+                                            uint32_t c1) {
+  uint16_t* slab = reinterpret_cast<uint16_t*>(slab32);
+  const int k = neg ? k0 - 1 : k0;         // k0 is even, or odd (flipped) for negative bins
+  const uint64_t v = neg ? ((uint64_t)c1 | ((uint64_t)c0 << 32)) : ((uint64_t)c0 | ((uint64_t)c1 << 32));
+  atomicAdd(reinterpret_cast<unsigned long long*>(slab + ((int64_t)m * kNBins + k) * 2), (unsigned long long)v);
+}
+
 // flush_hist_slots into a slab of 16-bit counters (PartTable::slab16): an LDS
 // word already holds the counts of experts e and e+1 (e = 4j + 2h) for one raw
 // bin, so the item's two words (raw bins 2b, 2b+1, kappa bins k, k+1 or k, k-1)
@@ -134,21 +145,15 @@ __device__ __forceinline__ void flush_hist_slots(uint32_t* sh, int32_t* __restri
 // the fields).
 template <int E>
 __device__ __forceinline__ void flush_hist_slots16(uint32_t* sh, int32_t* __restrict__ slab32) {
-  constexpr int kItems = fast_hist_words<E>() / 2;
-  uint16_t* slab = reinterpret_cast<uint16_t*>(slab32);
+  constexpr int kSlots = E / 4, kItems = 2 * (kNBins / 2) * kSlots;
   for (int i = threadIdx.x; i < kItems; i += blockDim.x) {
     const int it = flush_word(i, kItems);
-    const int arr = it >> 13, j = (it >> 6) & 127, slot = it & 63;
+    const int arr = it / (kItems / 2), j = it / kSlots % (kNBins / 2), slot = 64 - kSlots + it % kSlots;
     const int w0 = arr * 16384 + 2 * j * 64 + slot;
     const uint32_t c0 = sh[w0], c1 = sh[w0 + 64];
     if (c0 | c1) {
       const int m = 2 * (63 - slot) + arr;   // the pair of experts 2m, 2m+1
-      const bool neg = (2 * j) & 0x80;
-      const int k0 = kappa_hi_of_raw(2 * j);  // even, or odd (flipped) for negative bins
-      const int k = neg ? k0 - 1 : k0;
-      const uint64_t v = neg ? ((uint64_t)c1 | ((uint64_t)c0 << 32)) : ((uint64_t)c0 | ((uint64_t)c1 << 32));
-      atomicAdd(reinterpret_cast<unsigned long long*>(slab + ((int64_t)m * kNBins + k) * 2),
-                (unsigned long long)v);
+      add_words16(slab32, m, (2 * j) & 0x80, kappa_hi_of_raw(2 * j), c0, c1);
       sh[w0] = 0;
       sh[w0 + 64] = 0;
     }
@@ -194,7 +199,7 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
     const uint16_t* __restrict__ z, const float* __restrict__ b, int64_t T,
     int32_t* __restrict__ topk_idx, float* __restrict__ topk_score, float* __restrict__ tau,
     int32_t* __restrict__ load, int32_t* __restrict__ hist, const PartTable pt,
-    int64_t rows_per_block) {
+    int64_t rows_per_block, uint32_t* __restrict__ win, int slabs) {
   constexpr int G = FastCfg<E>::G;      // lanes per row
   constexpr int N = E / G;              // experts per lane
   constexpr int NQ = N / 4;             // 8-byte pieces per lane and row
@@ -267,8 +272,11 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
   }
 
   static_assert(fast_hist_words<E>() % 4 == 0, "16-byte zeroing");
-  for (int w = threadIdx.x; w < fast_hist_words<E>() / 4; w += kRouteBlock)
-    reinterpret_cast<uint4*>(sh_hist)[w] = make_uint4(0, 0, 0, 0);
+  // of the 64 slots of a bin the last E/4 are counted and read
+  constexpr int kRow4 = kSlotHist<E> ? E / 16 : fast_hist_words<E>() / 4;
+  constexpr int kRows = kSlotHist<E> ? 2 * kNBins : 1;
+  for (int w = threadIdx.x; w < kRows * kRow4; w += kRouteBlock)
+    reinterpret_cast<uint4*>(sh_hist)[kSlotHist<E> ? w / kRow4 * 16 + 16 - kRow4 + w % kRow4 : w] = make_uint4(0, 0, 0, 0);
   int fits = 1, bzero = 1;
   if (threadIdx.x == 0) sh_step = kRouteWaves;
   for (int e = threadIdx.x; e < E; e += kRouteBlock) {
@@ -693,10 +701,11 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
     seg_tau = tau + su;
   };
   // Adds the block's LDS counts (coarse bins, loads) of partition p to global
-  // memory and clears them.
+  // memory and clears them.  With an image the coarse counts stay until the
+  // block's rows are done.
   auto flush_counts = [&](int p) {
     __syncthreads();
-    if (hist) {
+    if (hist && !win) {
       if constexpr (kSlotHist<E>) {
         if (pt.slab16) flush_hist_slots16<E>(sh_hist, count_slab(hist, pt, p, E));
         else flush_hist_slots<E>(sh_hist, count_slab(hist, pt, p, E));
@@ -750,6 +759,62 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
   };
   if (keys_exact) sweep(std::true_type{});
   else sweep(std::false_type{});
+  if (win) {
+    // The flush's atomics, a thousand and more scattered 8-byte updates per block
+    // that every block of a launch makes at the same time, took 8 us of the 42 of
+    // 147,456 rows of E = 256.  Nearly all margins lie in a window of 16 of the
+    // 256 bins: the block stores those as one image (8 KiB at E = 256; images of
+    // all bins, 32 MiB in all, cost the selection more than they saved), and adds
+    // only the rest.  Layers, before -> after (us): E = 256 K = 6 147,456 tokens
+    // 64.6 -> 59.0, E = 128 K = 5 99,991 tokens 44.4 -> 39.1, K = 8 1,048,576 tokens
+    // 160 -> 156.5, E = 256 K = 16 65,537 tokens 56.0 -> 54.7; E = 64 and less even.
+    uint4* dst = reinterpret_cast<uint4*>(win + (int64_t)blockIdx.x * win_words(E));
+    for (int i = threadIdx.x; i < (E / 2) * (kWinBins / 4); i += kRouteBlock) {
+      const int m = i % (E / 2), q = i / (E / 2), raw = win_raw(4 * q);
+      const uint32_t* src = sh_hist + (kSlotHist<E> ? (m & 1) * 16384 + raw * 64 + 63 - (m >> 1) : m * kHistStride + raw);
+      constexpr int S = kSlotHist<E> ? 64 : 1;
+      dst[m * (kWinBins / 4) + q] = make_uint4(src[0], src[S], src[2 * S], src[3 * S]);
+    }
+    int32_t* slab = hist + (int64_t)(blockIdx.x % (unsigned)slabs) * E * kNBins;
+    // pairs of adjacent raw bins outside the window, four expert pairs at a time
+    // where they lie side by side
+    constexpr int kPairs = kNBins / 2 - kWinBins / 2;
+    constexpr int V = kSlotHist<E> ? 4 : 1, kGroups = E / 2 / V;
+    for (int i = threadIdx.x; i < kPairs * kGroups; i += kRouteBlock) {
+      const int group = i % kGroups, r = 2 * outside_pair(i / kGroups);
+      uint32_t c0[V], c1[V];
+      int m0;                              // expert pair of c0[0]; c0[v] is of pair m0 - 2v
+      if constexpr (kSlotHist<E>) {
+        const int arr = group & 1, slot = 64 - E / 4 + 4 * (group >> 1);
+        m0 = 2 * (63 - slot) + arr;
+        const uint32_t* src = sh_hist + arr * 16384 + r * 64 + slot;
+        const uint4 a = *reinterpret_cast<const uint4*>(src), c = *reinterpret_cast<const uint4*>(src + 64);
+        c0[0] = a.x; c0[1] = a.y; c0[2] = a.z; c0[3] = a.w;
+        c1[0] = c.x; c1[1] = c.y; c1[2] = c.z; c1[3] = c.w;
+      } else {
+        m0 = group;
+        c0[0] = sh_hist[m0 * kHistStride + r];
+        c1[0] = sh_hist[m0 * kHistStride + r + 1];
+      }
+      uint32_t any = 0;
+#pragma unroll
+      for (int v = 0; v < V; ++v) any |= c0[v] | c1[v];
+      if (any == 0) continue;
+      const bool neg = r & 0x80;
+      const int k0 = kappa_hi_of_raw(r);
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        if ((c0[v] | c1[v]) == 0) continue;
+        if (pt.slab16) {
+          add_words16(slab, m0 - 2 * v, neg, k0, c0[v], c1[v]);
+        } else {
+          int32_t* row = slab + (m0 - 2 * v) * 2 * kNBins;
+          if ((c0[v] | c1[v]) & 0xFFFFu) add_raw_pair(row, neg, c0[v] & 0xFFFFu, c1[v] & 0xFFFFu, k0);
+          if ((c0[v] | c1[v]) >> 16) add_raw_pair(row + kNBins, neg, c0[v] >> 16, c1[v] >> 16, k0);
+        }
+      }
+    }
+  }
 }
 
 // ----------------------------------------------------------- generic ----
@@ -832,27 +897,29 @@ __global__ __launch_bounds__(kBlock) void route_generic_kernel(
 
 // ------------------------------------------------------------- launch ---
 template <int E, int KT>
-void launch_fast(const RouteArgs& a, hipStream_t s, bool* slab16_used) {
+void launch_fast(const RouteArgs& a, hipStream_t s, RouteForm* form) {
   int blocks;
   int64_t rpb;
   grid_for(a.T, kRouteWaves * (64 / FastCfg<E>::G), 1, &blocks, &rpb);
   PartTable pt = a.pt;
-  pt.slab16 = (kSlotHist<E> && a.hist != nullptr && a.slab16_ok &&
-               slab_rows_bound(pt, rpb) <= kSegMax) ? 1 : 0;
-  if (slab16_used) *slab16_used = pt.slab16 != 0;
+  const bool images = a.win != nullptr && a.hist != nullptr && blocks <= a.win_blocks && rpb <= kSegMax;
+  const int nslabs = pt.P * pt.nsub, slabs = images ? (nslabs < kWinSlabs ? nslabs : kWinSlabs) : nslabs;
+  const int64_t slab_rows = images ? (int64_t)((blocks + slabs - 1) / slabs) * rpb : slab_rows_bound(pt, rpb);
+  pt.slab16 = (kSlotHist<E> && a.hist != nullptr && a.slab16_ok && slab_rows <= kSegMax) ? 1 : 0;
+  if (form) *form = RouteForm{pt.slab16 != 0, images ? blocks : 0, slabs};
   route_fast_kernel<E, KT><<<blocks, kRouteBlock, 0, s>>>(a.z, a.b, a.T, a.idx, a.score, a.tau, a.load,
-                                                     a.hist, pt, rpb);
+                                                     a.hist, pt, rpb, images ? a.win : nullptr, slabs);
 }
 
 // Every fan-out up to kFastKmax has its own kernel, the rounds unrolled.
 template <int E, int K>
-eqb_status launch_route_k(const RouteArgs& a, hipStream_t s, bool* slab16_used) {
+eqb_status launch_route_k(const RouteArgs& a, hipStream_t s, RouteForm* form) {
   if constexpr (K <= kFastKmax && K < E) {
     if (a.K == K) {
-      launch_fast<E, K>(a, s, slab16_used);
+      launch_fast<E, K>(a, s, form);
       return launch_status();
     }
-    return launch_route_k<E, K + 1>(a, s, slab16_used);
+    return launch_route_k<E, K + 1>(a, s, form);
   } else {
     int blocks;
     int64_t rpb;
@@ -864,12 +931,12 @@ eqb_status launch_route_k(const RouteArgs& a, hipStream_t s, bool* slab16_used) 
 }
 
 template <int E>
-eqb_status launch_route_e(const RouteArgs& a, hipStream_t s, bool* slab16_used) {
-  if (slab16_used) *slab16_used = false;
-  return launch_route_k<E, 1>(a, s, slab16_used);
+eqb_status launch_route_e(const RouteArgs& a, hipStream_t s, RouteForm* form) {
+  if (form) *form = RouteForm{false, 0, a.pt.P * a.pt.nsub};
+  return launch_route_k<E, 1>(a, s, form);
 }
 
 // This file is compiled once per expert count, the objects side by side.
-template eqb_status launch_route_e<EQB_ROUTE_E>(const RouteArgs& a, hipStream_t s, bool* slab16_used);
+template eqb_status launch_route_e<EQB_ROUTE_E>(const RouteArgs& a, hipStream_t s, RouteForm* form);
 
 }  // namespace eqb

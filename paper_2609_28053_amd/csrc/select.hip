@@ -17,13 +17,16 @@ namespace eqb {
 // Each counter is read and cleared by the same thread.
 // kSlab16 (the layer, global form): the P slabs hold 16-bit counters in the
 // layout of PartTable::slab16; each is read, summed and cleared as a uint16.
+// images > 0 (the layer): the counts of the window's bins come from that many
+// block images at win as well.
 template <bool kLocal, bool kSlab16 = false>
 __global__ __launch_bounds__(kNBins) void select_coarse_kernel(
     int32_t* __restrict__ hist, int P, int E, int K, int64_t r, const PartTable pt,
     int32_t* __restrict__ sel_hi, int64_t* __restrict__ rank_in_bin, int32_t* __restrict__ hist_sum,
     int32_t* __restrict__ status, bool clear = false, int32_t* __restrict__ load_acc = nullptr,
-    int32_t* __restrict__ load_out = nullptr) {
+    int32_t* __restrict__ load_out = nullptr, const uint32_t* __restrict__ win = nullptr, int images = 0) {
   __shared__ int64_t sh[kNBins];
+  __shared__ uint32_t sh_win[kNBins / 64][kWinBins];
   const int e = blockIdx.x, u = threadIdx.x, p = kLocal ? (int)blockIdx.y : 0;
   const int64_t out = kLocal ? (int64_t)p * E + e : e;
   if (kLocal) {
@@ -41,6 +44,40 @@ __global__ __launch_bounds__(kNBins) void select_coarse_kernel(
   if (kLocal) {
     c = hist[((int64_t)p * E + e) * kNBins + u];
   } else {
+    if (images > 0) {
+      // thread u reads words 4 (u % 4) .. + 3 of the pair's row of images u / 4, + 64, ..
+      const int half = (e & 1) * 16;
+      const uint4* src = reinterpret_cast<const uint4*>(win + (int64_t)(e >> 1) * kWinBins) + (u & 3);
+      const int64_t step = win_words(E) / 4;
+      uint32_t s[4] = {0, 0, 0, 0};
+      auto add = [&](const uint4& v) {
+        s[0] += (v.x >> half) & 0xFFFFu;
+        s[1] += (v.y >> half) & 0xFFFFu;
+        s[2] += (v.z >> half) & 0xFFFFu;
+        s[3] += (v.w >> half) & 0xFFFFu;
+      };
+      int i = u >> 2;
+      for (; i + 192 < images; i += 256) {
+        uint4 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = src[(i + 64 * j) * step];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) add(v[j]);
+      }
+      for (; i < images; i += 64) add(src[i * step]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+#pragma unroll
+        for (int d = 4; d < 64; d <<= 1) s[j] += __shfl_xor(s[j], d);
+        if ((u & 63) < 4) sh_win[u >> 6][4 * (u & 3) + j] = s[j];
+      }
+      __syncthreads();
+      const int w = win_place(raw_hi_of_kappa(u));
+      if (w >= 0) {
+#pragma unroll
+        for (int j = 0; j < kNBins / 64; ++j) c += sh_win[j][w];
+      }
+    }
     if (kSlab16) {
       uint16_t* h16 = reinterpret_cast<uint16_t*>(hist) + ((int64_t)(e >> 1) * kNBins + u) * 2 + (e & 1);
       const int64_t stride = (int64_t)E * kNBins * 2;  // one int32 slab, in 16-bit units
@@ -56,7 +93,7 @@ __global__ __launch_bounds__(kNBins) void select_coarse_kernel(
       if (clear)
         for (int q2 = 0; q2 < P; ++q2) h16[q2 * stride] = 0;
     } else {
-      c = slab_sum(hist + (int64_t)e * kNBins + u, P, (int64_t)E * kNBins);
+      c += slab_sum(hist + (int64_t)e * kNBins + u, P, (int64_t)E * kNBins);
       if (clear) slab_clear(hist + (int64_t)e * kNBins + u, P, (int64_t)E * kNBins);
     }
     if (hist_sum) hist_sum[(int64_t)e * kNBins + u] = (int32_t)c;
@@ -318,17 +355,18 @@ __global__ __launch_bounds__(kPartThreads) void select_fine_parts_kernel(
 eqb_status launch_layer_selects(int pass, int32_t* hist, int P, int nsub, int E, int64_t r, int32_t* sel_hi,
                                 int64_t* rank_in_bin, uint16_t* q_bf16, float* b_next,
                                 int32_t* hist_sum, int32_t* load_acc, int32_t* load_out, int32_t* status,
-                                int32_t* ticket, hipStream_t s, bool slab16) {
+                                int32_t* ticket, hipStream_t s, RouteForm form, const uint32_t* win) {
   PartTable none{};
   none.P = P;
-  const int nslabs = P * nsub;
+  const int nslabs = pass == 1 ? form.slabs : P * nsub;
   if (pass == 1) {
-    if (slab16)
+    if (form.slab16)
       select_coarse_kernel<false, true><<<E, kNBins, 0, s>>>(hist, nslabs, E, 0, r, none, sel_hi, rank_in_bin,
-                                                             hist_sum, nullptr, true, load_acc, load_out);
+                                                             hist_sum, nullptr, true, load_acc, load_out, win,
+                                                             form.images);
     else
       select_coarse_kernel<false><<<E, kNBins, 0, s>>>(hist, nslabs, E, 0, r, none, sel_hi, rank_in_bin, hist_sum,
-                                                       nullptr, true, load_acc, load_out);
+                                                       nullptr, true, load_acc, load_out, win, form.images);
     return launch_status();
   }
   select_fine_kernel<false, true><<<E, kNBins, 0, s>>>(hist, nslabs, E, none, sel_hi, rank_in_bin, nullptr, q_bf16,
@@ -359,13 +397,15 @@ eqb_status launch_layer(const RouteArgs& route, int64_t r, const LayerWorkspace&
   a.slab16_ok = true;
   eqb_status st = mark(marks, 0, s);
   if (st != EQB_OK) return st;
-  bool slab16 = false;
-  st = launch_route(a, s, &slab16);
+  a.win = w.part;                   // consumed before the fine pass stores its images there
+  a.win_blocks = w.part_blocks;
+  RouteForm form;
+  st = launch_route(a, s, &form);
   if (st != EQB_OK) return st;
   if ((st = mark(marks, 1, s)) != EQB_OK) return st;
   const int P = a.pt.P, E = a.E;
   st = launch_layer_selects(1, w.hist_hi, P, w.nsub, E, r, w.sel_hi, w.rank_in_bin, nullptr, nullptr,
-                            hist_hi_sum, w.load_acc, load_out, nullptr, nullptr, s, slab16);
+                            hist_hi_sum, w.load_acc, load_out, nullptr, nullptr, s, form, w.part);
   if (st != EQB_OK) return st;
   if ((st = mark(marks, 2, s)) != EQB_OK) return st;
   MarginArgs m;
