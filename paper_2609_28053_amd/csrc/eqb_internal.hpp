@@ -119,7 +119,7 @@ eqb_status launch_lei_inject(float* grad, const float* inj, int64_t T, int E, co
 // when the fine pass stores per-block images, and the coarse selection reads
 // and clears every slab: 8 measured faster than 16, 4, 2 or 1 at one
 // partition of 147,456 tokens (1.2% against 16), and no slower on the other
-// workloads.
+// workloads.  With images (RouteForm) the route sweep uses kWinSlabs of them.
 inline int layer_replicas(int P) { return P >= 8 ? 1 : 8 / P; }
 
 // Working buffers of one layer (eqb_layer): the per-partition coarse and
