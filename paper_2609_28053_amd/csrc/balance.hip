@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kBwdBlock, 8) void lei_router_backward_kernel(
   constexpr int R = 64 / G;
   constexpr uint32_t ROWS = kBwdWaves * R * kBwdU;
   __shared__ __align__(16) float sh_g[kBwdWaves][kBwdU][R][E];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane % G, rr = lane / G;
   float* my = &sh_g[wave][0][rr][0];      // row u of this lane: my + u * R * E
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -194,8 +194,10 @@ __global__ __launch_bounds__(kBwdBlock, 8) void lei_router_backward_kernel(
     const uint32_t n = (uint32_t)(s1 - s0);
     f32x4 d = zero;
     if (inj) {
-      const float* di = inj + (int64_t)p * E + 4 * g;
-      d = f32x4{di[0], di[1], di[2], di[3]};
+      const float* di = inj + wave_uniform((int64_t)p * E);
+      uint32_t o = 16u * g;
+      asm volatile("" : "+v"(o));
+      d = f32x4{at<const float>(di, o), at<const float>(di, o + 4), at<const float>(di, o + 8), at<const float>(di, o + 12)};
     }
     auto row_of = [&](uint32_t base, int u) -> uint32_t { return base + (uint32_t)((wave * kBwdU + u) * R + rr); };
     // logits and this lane's pair of its rows at step base
@@ -218,8 +220,12 @@ __global__ __launch_bounds__(kBwdBlock, 8) void lei_router_backward_kernel(
     u32x2 zn[kBwdU];
     int en[kBwdU];
     float gn[kBwdU];
-    load(0, zn, en, gn);
-    for (uint32_t base = 0; base < n; base += ROWS) {
+    // opaque: the first step's lane offsets, formed here rather than kept (as 64-bit
+    // addresses) in registers across the segments
+    uint32_t first = 0;
+    asm volatile("" : "+s"(first));
+    load(first, zn, en, gn);
+    for (uint32_t base = first; base < n; base += ROWS) {
       u32x2 zw[kBwdU];
       int ec[kBwdU];
       float gc[kBwdU];
@@ -230,6 +236,16 @@ __global__ __launch_bounds__(kBwdBlock, 8) void lei_router_backward_kernel(
         gc[u] = gn[u];
       }
       if (base + ROWS < n) load(base + ROWS, zn, en, gn);
+      // Logits of 32 or more take a longer form, chosen per wave and step, so that the
+      // usual step has 12 instructions per sigmoid'.  Both work from the registers: with
+      // one logit in a hundred above 32, 1,000,003 rows of E = 128, K = 8 take 158.1 us,
+      // and 155.1 without any (computing such logits again from memory one by one, after
+      // the stores, took 402; normal logits of deviation 64, most steps: 592 -> 158).
+      float zmax = 0.0f;
+#pragma unroll
+      for (int u = 0; u < kBwdU; ++u)
+        zmax = max3_abs(max3_abs(zmax, bf16_lo(zw[u].x), bf16_hi(zw[u].x)), bf16_lo(zw[u].y), bf16_hi(zw[u].y));
+      const bool large = __any(zmax >= kSigmoidMax);
       // scatter the rows' mixture gradients
 #pragma unroll
       for (int u = 0; u < kBwdU; ++u) {
@@ -244,31 +260,31 @@ __global__ __launch_bounds__(kBwdBlock, 8) void lei_router_backward_kernel(
         }
       }
       lds_wave_sync();
-      float zmax = 0.0f;
+      auto write = [&](auto wide) __attribute__((always_inline)) {
 #pragma unroll
-      for (int u = 0; u < kBwdU; ++u) {
-        const uint32_t t = row_of(base, u);
-        const f32x4 gm = place(u);
-        const float zf[4] = {bf16_lo(zw[u].x), bf16_hi(zw[u].x), bf16_lo(zw[u].y), bf16_hi(zw[u].y)};
-        f32x4 o;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = (gm[j] + d[j]) * sigmoid_prime_bf16(zf[j]);
-        zmax = max3_abs(max3_abs(zmax, zf[0], zf[1]), zf[2], zf[3]);
-        if (t < n) __builtin_nontemporal_store(o, &at<f32x4>(seg_gz, (t * E + 4 * g) * 4u));
-      }
-      // logits of 32 or more (rare): the lane computes those again, one by one
-      if (__builtin_expect(__any(!(zmax < kSigmoidMax)), 0)) {
-#pragma unroll 1
-        for (int i = 0; i < kBwdU * 4; ++i) {
-          const int u = i >> 2, e = 4 * g + (i & 3);
+        for (int u = 0; u < kBwdU; ++u) {
           const uint32_t t = row_of(base, u);
-          if (t >= n) continue;
-          const float zf = bf16_lo(seg_z[t * E + e]);
-          if (fabsf(zf) < kSigmoidMax) continue;
-          const float di = inj ? inj[(int64_t)p * E + e] : 0.0f;
-          seg_gz[t * E + e] = (my[u * R * E + e] + di) * sigmoid_prime_fast(zf);
+          uint32_t w0 = zw[u].x, w1 = zw[u].y;
+          // nothing of the usual form is kept, and no row begun before the last is stored: registers
+          if (decltype(wide)::value) asm volatile("" : "+v"(w0), "+v"(w1)::"memory");
+          const f32x4 gm = place(u);
+          const float zf[4] = {bf16_lo(w0), bf16_hi(w0), bf16_lo(w1), bf16_hi(w1)};
+          f32x4 o;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            o[j] = (gm[j] + d[j]) * sigmoid_prime_bf16<decltype(wide)::value>(zf[j]);
+            if (decltype(wide)::value) __builtin_amdgcn_sched_barrier(0);
+          }
+          if (t < n) {
+            __builtin_nontemporal_store(o, &at<f32x4>(seg_gz, (t * E + 4 * g) * 4u));
+            // keeps the compiler from sinking the ends of both forms into one block
+            if (decltype(wide)::value) asm volatile("; large logits");
+            else asm volatile("; usual logits");
+          }
         }
-      }
+      };
+      if (__builtin_expect(large, 0)) write(std::true_type{});
+      else write(std::false_type{});
       if (kOnePair) lds_wave_sync();   // every place has been read
 #pragma unroll
       for (int u = 0; u < kBwdU; ++u) {

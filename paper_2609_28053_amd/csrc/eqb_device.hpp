@@ -113,29 +113,22 @@ __device__ __forceinline__ float sigmoid_fast(float x) {
   return x >= 0.0f ? r : e * r;
 }
 
-// sigmoid'(x) = e / (1 + e)^2 with e = exp(-|x|) (the form that keeps its
-// relative accuracy for large |x|), e from the same split base-2 exponential
-// of any binary32 x; a few ulp for |x| <= 64, the libm exponential beyond.
-__device__ __forceinline__ float sigmoid_prime_fast(float x) {
-  const float a = fabsf(x);
-  float e;
-  if (a > 64.0f) {
-    e = expf(-a);
-  } else {
-    const float kLog2eHi = 1.44269502162933349609375f;
-    const float kLog2eLo = 1.925963033500011e-08f;
-    const float kLn2 = 0.693147180559945309f;
-    const float p_hi = a * kLog2eHi;
-    const float p_lo = __builtin_fmaf(a, kLog2eLo, __builtin_fmaf(a, kLog2eHi, -p_hi));
-    const float e1 = __builtin_amdgcn_exp2f(-p_hi);
-    e = __builtin_fmaf(-e1, p_lo * kLn2, e1);
-  }
-  const float r = 1.0f / (1.0f + e);
-  return e * r * r;
+// The same of any BF16 a >= 0.  From a = 32 the second factor is 1 - c + c^2/2 (off by
+// c^3/6 < 5e-11 up to a = 128, where the result is 0).  From a = 64 the hardware
+// exponential, which has no subnormal results, gives 2^64 times the value (the
+// argument's sum is exact), and the scaling rounds once.
+__device__ __forceinline__ float exp_neg_bf16_wide(float a) {
+  const float kHi = 1.44268798828125f;
+  const float kLoLn2 = 4.888495368504664e-06f;
+  a = a > 128.0f ? 128.0f : a;
+  const bool up = a >= 64.0f;
+  const float c = a * kLoLn2, h = a >= kSigmoidMax ? -0.5f : 0.0f;
+  const float e1 = __builtin_amdgcn_exp2f((up ? 64.0f : 0.0f) - a * kHi);
+  return __builtin_amdgcn_ldexpf(__builtin_fmaf(-e1, __builtin_fmaf(c * h, c, c), e1), up ? -64 : 0);
 }
 
-// sigmoid'(x) of a BF16 x with |x| < 32, in 12 instructions where the form above
-// takes about 30 (an IEEE division, two products to split x log2 e, a test).
+// sigmoid'(x) = e / (1 + e)^2, e = exp(-|x|), of a BF16 x with |x| < 32, in 12
+// instructions (with an IEEE division and x log2 e split into two products: 30).
 // 1 + e lies in [1, 2]: the hardware reciprocal (1 ulp) and one Newton step round
 // like the division but for rare last bits, and with q = sigmoid(-a), q - q^2 in
 // one rounding halves what q carries near 0.
@@ -144,8 +137,10 @@ __device__ __forceinline__ float max3_abs(float m, float a, float b) {
   asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(m), "v"(a), "v"(b));
   return r;
 }
+// wide: any BF16 x, in 20 instructions; for |x| < 32 the same value.
+template <bool wide>
 __device__ __forceinline__ float sigmoid_prime_bf16(float x) {
-  const float e = exp_neg_bf16(fabsf(x));
+  const float e = wide ? exp_neg_bf16_wide(fabsf(x)) : exp_neg_bf16(fabsf(x));
   const float d = 1.0f + e;
   const float r0 = __builtin_amdgcn_rcpf(d);
   const float q = e * __builtin_fmaf(__builtin_fmaf(-d, r0, 1.0f), r0, r0);   // sigmoid(-a) <= 1/2
