@@ -121,7 +121,8 @@ __global__ __launch_bounds__(kNBins) void select_coarse_kernel(
 // exponents span at most 36 every partial sum in any order is below 2^(8 + 1 +
 // emax) and a multiple of 2^(emin - 7), 53 bits at most: exact, and equal to the
 // ascending sum.  Then the waves sum in parallel; a wider span (or a NaN) is
-// summed one by one, 256 dependent additions.
+// summed one by one, 256 dependent additions.  The ascending sum begins with +0, which
+// makes a sum of nothing but -0 +0; so does the last addition here.
 __device__ __forceinline__ double ascending_sum(const double* val, int E, double* sh, int* shx) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (wave < 4) {
@@ -143,7 +144,7 @@ __device__ __forceinline__ double ascending_sum(const double* val, int E, double
   __syncthreads();
   const int lo = min(min(shx[0], shx[2]), min(shx[4], shx[6]));
   const int hi = max(max(shx[1], shx[3]), max(shx[5], shx[7]));
-  if (hi - lo <= 36) return ((sh[0] + sh[1]) + sh[2]) + sh[3];
+  if (hi - lo <= 36) return 0.0 + (((sh[0] + sh[1]) + sh[2]) + sh[3]);
   double acc = 0.0;
   for (int e = 0; e < E; ++e) acc += val[e];
   return acc;

@@ -21,14 +21,9 @@ def ascending(bhat):
     return (bhat - acc / len(bhat)).astype(np.float32)
 
 
-@pytest.mark.parametrize("E", [8, 64, 256])
-@pytest.mark.parametrize("span", [0, 20, 35, 36, 37, 38, 60, 200])
-def test_centring(eqb, E, span):
-    rng = np.random.default_rng(100 * E + span)
-    exp = rng.integers(20, 21 + span, E)               # biased BF16 exponents
-    exp[:2] = (20, 20 + span)
-    bits = (rng.integers(0, 2, E) << 15 | exp << 7 | rng.integers(0, 128, E)).astype(np.uint32)
-    bits[3] = 0x8000                                   # a zero does not count to the span
+def centre(eqb, bits):
+    """q_bf16 (checked) and b_next for quantiles of these BF16 patterns."""
+    E = len(bits)
     key = np.where(bits & 0x8000, bits ^ 0xFFFF, bits ^ 0x8000)
     hist = np.zeros((1, E, 256), np.int32)
     hist[0, np.arange(E), key & 0xFF] = 1
@@ -39,5 +34,27 @@ def test_centring(eqb, E, span):
     b_next = torch.empty(E, dtype=torch.float32, device="cuda")
     eqb.eqb_select_quantile(2, i32(hist), 1, i32(key >> 8), rank, sel_lo, q, b_next)
     assert np.array_equal(q.cpu().numpy().view(np.uint16), bits.astype(np.uint16))
+    return b_next.cpu().numpy()
+
+
+@pytest.mark.parametrize("E", [8, 64, 256])
+@pytest.mark.parametrize("span", [0, 20, 35, 36, 37, 38, 60, 200])
+def test_centring(eqb, E, span):
+    rng = np.random.default_rng(100 * E + span)
+    exp = rng.integers(20, 21 + span, E)               # biased BF16 exponents
+    exp[:2] = (20, 20 + span)
+    bits = (rng.integers(0, 2, E) << 15 | exp << 7 | rng.integers(0, 128, E)).astype(np.uint32)
+    bits[3] = 0x8000                                   # a zero does not count to the span
     bhat = (bits << 16).astype(np.uint32).view(np.float32).astype(np.float64)
-    assert np.array_equal(b_next.cpu().numpy().view(np.uint32), ascending(bhat).view(np.uint32))
+    assert np.array_equal(centre(eqb, bits).view(np.uint32), ascending(bhat).view(np.uint32))
+
+
+@pytest.mark.parametrize("E", [8, 64, 128, 256])
+@pytest.mark.parametrize("zeros", ["plus", "minus", "both"])
+def test_centring_zeros(eqb, E, zeros):
+    """Quantiles that are all zeros: the ascending sum is +0 whatever their signs."""
+    bits = np.full(E, 0x8000 if zeros == "minus" else 0, np.uint32)
+    if zeros == "both":
+        bits[::2] = 0x8000
+    bhat = (bits << 16).astype(np.uint32).view(np.float32).astype(np.float64)
+    assert np.array_equal(centre(eqb, bits).view(np.uint32), ascending(bhat).view(np.uint32))
