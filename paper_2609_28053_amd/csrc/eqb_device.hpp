@@ -231,9 +231,11 @@ __device__ __forceinline__ int key_max(int a, int b) {
   asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
 }
+// min(a, b), or -inf where b is no number (the median of three operands with a NaN is
+// the least of the others): the key of a logit of -inf, which enters no list.
 __device__ __forceinline__ int key_min(int a, int b) {
   int r;
-  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  asm("v_med3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(kKeyNone), "v"(b));
   return r;
 }
 __device__ __forceinline__ int key_med3(int a, int b, int c) {

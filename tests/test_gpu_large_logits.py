@@ -1,4 +1,4 @@
-"""Router backward on logits of every magnitude: sigmoid' over all finite BF16
+"""Router backward on logits of every magnitude: sigmoid' over all BF16
 values against binary64, and the time of a batch in which some logits are large."""
 import numpy as np
 import pytest
@@ -10,15 +10,15 @@ from timing import median_us
 pytestmark = pytest.mark.gpu
 
 
-def test_every_finite_logit(eqb):  # noqa: F811
+def test_every_logit(eqb):  # noqa: F811
     """grad_z = sigmoid'(z) where inj = 1 and no pair is selected.  Tolerance: an ulp
     of the exponential and 1.3e-8 of its correction, an ulp of the reciprocal and three
     roundings, 3e-7 in all; a subnormal result is rounded once more, by half of 2^-149."""
     E, T, K = 256, 256, 1
     bits = np.arange(1 << 16, dtype=np.uint32).astype(np.uint16)
-    bits[(bits & 0x7F80) == 0x7F80] = 0
+    bits[(bits & 0x7FFF) > 0x7F80] = 0                  # infinities stay: masked experts
     z = np.random.default_rng(0).permutation(bits).reshape(T, E)
-    say("router backward, every finite logit")
+    say("router backward, every logit")
     gz = torch.empty((T, E), dtype=torch.float32, device="cuda")
     eqb.eqb_lei_router_backward(torch.from_numpy(z.view(np.int16)).cuda(),
                                 torch.full((T, K), -1, dtype=torch.int32, device="cuda"),
