@@ -902,6 +902,13 @@ void launch_fast(const RouteArgs& a, hipStream_t s, RouteForm* form) {
   int64_t rpb;
   grid_for(a.T, kRouteWaves * (64 / FastCfg<E>::G), 1, &blocks, &rpb);
   PartTable pt = a.pt;
+  if (a.hist == nullptr && a.load == nullptr) {
+    // nothing is counted per partition: one segment, where each of a block's would
+    // end in barriers and start with nothing in flight (1,021 rows of E = 64 in 16
+    // partitions: 13.4 us, 10.1 as one)
+    pt.P = 1;
+    pt.off[1] = a.T;
+  }
   const bool images = a.win != nullptr && a.hist != nullptr && blocks <= a.win_blocks && rpb <= kSegMax;
   const int nslabs = pt.P * pt.nsub, slabs = images ? (nslabs < kWinSlabs ? nslabs : kWinSlabs) : nslabs;
   const int64_t slab_rows = images ? (int64_t)((blocks + slabs - 1) / slabs) * rpb : slab_rows_bound(pt, rpb);
