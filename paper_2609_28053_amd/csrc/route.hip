@@ -19,25 +19,24 @@
 // E = 128, K = 5); the largest head left is rank K+1.  A lane whose list runs
 // dry is scanned once for its next key, and a row whose rounds missed a key
 // is extracted again with refilled lists.  Key order is
-// score order except between scores that agree in their top 24 bits;
-// extraction continues until the last key leaves the top-24-bit run of rank
-// K, the winners' exact scores are recomputed from z and b, and a row whose
-// extracted scores are not in exact order is sorted exactly.  A block whose
-// bias has |b| >= 2^119 (where z + b could overflow) takes the exact 64-bit
-// path for every row.
+// score order except between scores that agree in their top 24 bits.  Where the
+// run of rank K's top 24 bits continues past it, its members for the ranks up to K
+// are chosen among the whole run by the 16 bits that order it (the scores' low
+// bytes, the indices); where neighbours among the ranks agree, their exact scores
+// are recomputed from z and b and every rank takes its place by counting the
+// greater ones.  A block whose bias has |b| >= 2^119 (where z + b could overflow)
+// takes the exact 64-bit path for every row.
 //
 // Generic kernel (any K < E): K+1 rounds over exact 64-bit keys.
 #include "eqb_internal.hpp"
 
 namespace eqb {
 
-constexpr int kFastKmax = 16;          // widest fan-out of the fast kernel
-// Ranks kept per row: K + 1 and the run of rank K's top 24 bits.  A longer run
-// sends its row to the exact 64-bit path, 25 us of its wave at K = 14: with room
-// for one rank more than K + 1 such a row came once in about a thousand of
-// random logits, with two once in a million.  At E = 64 (16 rows per wave) the
-// LDS holds 19 ranks next to the counts.
-template <int E, int K> constexpr int rank_room() { return K <= 13 ? 16 : E == 64 ? 19 : 24; }
+// Widest fan-out of the fast kernel.  Every fan-out is a kernel of its own per E, about
+// 80 KB of code at E = 256, and no configuration here routes to more than 16 experts; neither
+// LDS nor registers set the line.  65,537 tokens of E = 256: K = 16 53 us, K = 17 (generic
+// kernel) 171.
+constexpr int kFastKmax = 16;
 // Sorted keys kept per lane: the rounds pop at most K+1 keys of a lane and
 // look at one more, and a lane holds N = E/G keys in all, so min(N, K + 2)
 // never runs dry.  Fewer levels cost less per element (one instruction each);
@@ -204,12 +203,10 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
   constexpr int N = E / G;              // experts per lane
   constexpr int NQ = N / 4;             // 8-byte pieces per lane and row
   constexpr int R = 64 / G;             // rows per wave
-  constexpr int kRmax = rank_room<E, KT>();
-  constexpr int RSLOT = (kRmax + G - 1) / G;  // rank slots per lane, staged rows
-  constexpr int HSLOT = (KT + G) / G;         // rank slots per lane, ranks 0..K
+  constexpr int HSLOT = (KT + G) / G;   // rank slots per lane, ranks 0..K
   constexpr int K = KT;
   static_assert(N % 4 == 0 && N >= 8, "layout");
-  static_assert(KT >= 1 && KT < E && KT <= kFastKmax, "K+1 keys exist and fit the rank buffer");
+  static_assert(KT >= 1 && KT < E && KT <= kFastKmax, "K+1 keys exist");
   constexpr int kList = list_depth<E, KT>();
 
   __shared__ __align__(16) uint32_t sh_hist[fast_hist_words<E>()];
@@ -220,7 +217,8 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
   // with one 16-byte read per lane, and copies E words apart (a multiple of
   // the 64 banks) would put every row's reads on the same 32 banks.
   __shared__ float sh_bk[NQ][E + kBiasPad];
-  __shared__ uint2 sh_rank[kRouteWaves][R][kRmax];   // (score bits, zbits << 16 | e) in rank order
+  // staged rows: exact keys (first routing keys) by rank; an odd stride spreads the rows over the banks
+  __shared__ uint64_t sh_rank[kRouteWaves][R][(KT + 1) | 1];
   __shared__ uint32_t sh_step;                        // next unclaimed wave step of the segment
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -299,16 +297,16 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
   // ones).
   const bool keys_exact = __syncthreads_and(bzero) != 0;
 
-  uint2* myrank = sh_rank[wave][r];
+  uint64_t* myrank = sh_rank[wave][r];
 
-  // key of element (q, i) from its widened logit
-  auto key_of = [&](float zf, float bv, uint32_t ipk, int i) -> int {
-    const uint32_t sb = __float_as_uint(zf + bv);
-    return (int)__builtin_amdgcn_perm(sb, ipk, 0x07060500u | (uint32_t)i);
+  // key of element (q, i) from its score
+  auto key_of = [&](float score, uint32_t ipk, int i) -> int {
+    return (int)__builtin_amdgcn_perm(__float_as_uint(score), ipk, 0x07060500u | (uint32_t)i);
   };
 
-  // Rebuild a lane's sorted list from its keys strictly below thr.
-  auto rebuild = [&](const float (&zf)[N], int thr, int (&L)[kList]) __attribute__((always_inline)) {
+  // Rebuild a lane's sorted list from the values key(sum, index bytes, i) of its
+  // experts that are strictly below thr.
+  auto rebuild = [&](const float (&zf)[N], int thr, int (&L)[kList], auto&& key) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < kList; ++j) L[j] = kKeyNone;
 #pragma unroll
@@ -317,9 +315,10 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
       const uint32_t ipk = idxpk(q);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int x = key_of(zf[q * 4 + i], pick(bq, i), ipk, i);
+        const int x = key(zf[q * 4 + i] + pick(bq, i), ipk, i);
         list_insert(L, key_lt(x, thr) ? x : kKeyNone);
       }
+      __builtin_amdgcn_sched_barrier(0);   // one piece's keys and biases at a time: registers
     }
   };
 
@@ -359,7 +358,7 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
       const uint32_t ipk = idxpk(q);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        list_insert_at(L, key_of(zf[q * 4 + i], pick(bq, i), ipk, i), q * 4 + i);
+        list_insert_at(L, key_of(zf[q * 4 + i] + pick(bq, i), ipk, i), q * 4 + i);
       bq = bn;
     }
 
@@ -370,10 +369,9 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
       for (int j = 0; j < kList - 1; ++j) L[j] = win ? L[j + 1] : L[j];
       L[kList - 1] = win ? kKeyNone : L[kList - 1];
     };
-    // Rows whose ranks are staged in LDS: run past rank K+1, equal top-24-bit
-    // keys or a list that ran dry; (slow) rows the keys cannot settle.
+    // Rows whose ranks are staged in LDS: a run that continues past rank K, equal
+    // top-24-bit keys or a list that ran dry; (slow) rows of a bias beyond 2^119.
     bool staged = false, slow = false;
-    int nrank = 0;
     float tv = 0.0f;          // tau of this lane's row (common rows)
     int rk[HSLOT];
     uint32_t zown[HSLOT];
@@ -417,8 +415,8 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
         const uint32_t ipk = idxpk(q);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int x = key_of(zf[q * 4 + i], pick(bq, i), ipk, i);
-          nxt = key_lt(x, tail) ? key_max(nxt, x) : nxt;
+          const int x = key_of(zf[q * 4 + i] + pick(bq, i), ipk, i);
+          nxt = key_max(nxt, key_lt(x, tail) ? x : kKeyNone);
         }
       }
       hk = dry_lane ? nxt : hk;
@@ -468,11 +466,9 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
         zown[s] = zl;
       }
     }
-    const int tauhi = mK >> 8;
     const bool dry = rowflag == 2;   // the rounds missed a key of a dry lane
     slow = valid && !bias_ok;
     staged = valid && !slow && (near || rowflag != 0);
-    nrank = K + 1;
     // A row is staged when adjacent ranks' keys agree in their top 24 bits
     // (their order may be wrong) or the run of rank K's top 24 bits
     // continues past it.  With exact keys such keys hold equal scores, and
@@ -480,115 +476,112 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
     // the index byte already orders them as the exact order does: only a
     // missed key needs the staged path.
     if constexpr (decltype(exact)::value) staged = staged && (dry || mK < 0);
+    // ---- staged rows: the K + 1 keys by rank, those of rank K's run chosen and
+    // the others ordered by their exact scores
     if (__builtin_expect(__any(staged), 0)) {
-      // stage the keys, extend the run of rank K if it continues, then exact scores
 #pragma unroll
       for (int s = 0; s < HSLOT; ++s) {
         const int k = s * G + g;
-        if (staged && k <= K) myrank[k].x = (uint32_t)rk[s];
+        if (staged && k <= K) myrank[k] = (uint32_t)rk[s];
       }
-      // the keys past rank K are taken from lists rebuilt below mK, while
-      // they share the top 24 bits of rank K
-      bool ext = staged && rowflag == 1;
-      bool bad = false;           // row-uniform: extraction can no longer be trusted
-      if (__any(ext)) {
-        rebuild(zf, mK, L);
-        for (int k = K + 1; k < kRmax; ++k) {
-          if (!__any(ext)) break;
-          // a lane whose list ran dry may hold the next key
-          const bool dry_now = group_max_i32<G>((int)(L[0] == kKeyNone)) != 0;
-          if (ext && dry_now) {
-            bad = true;
-            ext = false;
-          }
-          const int M = group_max_key<G>(L[0]);
-          if (ext) {
-            if (g == 0) myrank[k].x = (uint32_t)M;
-            nrank = k + 1;
-            if ((M >> 8) != tauhi) ext = false;
-          }
-          pop(M);
-        }
-      }
-      bad = bad || ext;           // the run is longer than the rank buffer
-      // Rows whose rounds missed a key (a lane held more of the top K+1
-      // keys than its list) redo the extraction from fresh lists, refilling
-      // a lane's list below its last key whenever it runs dry again (as the
-      // generic-K loop does); only a run longer than the rank buffer still
-      // goes to the exact 64-bit path.
-      bool redo = staged && dry;
+      // Rows whose rounds missed a key (a lane held more of the top K+1 keys
+      // than its list) are extracted again, a lane's list refilled below the last
+      // rank whenever it is empty.
+      const bool redo = staged && dry;
       if (__any(redo)) {
-        if (redo) rebuild(zf, kKeyTop, L);
-        bool done = !redo;
-        int th = 0;
+        bool need = redo;
+        int M = kKeyTop;
 #pragma unroll 1
-        for (int k = 0; k < kRmax; ++k) {
-          if (!__any(!done)) break;
-          const int M = group_max_key<G>(L[0]);
-          pop(M);
-          const bool dl = (L[0] == kKeyNone) && (M != kKeyNone);
-          if (__any(dl && !done)) {
-            if (dl && !done) rebuild(zf, M, L);
+        for (int k = 0; k <= K; ++k) {
+          if (__any(need)) {
+            if (need) rebuild(zf, M, L, key_of);
           }
-          if (!done) {
-            if (M == kKeyNone) {
-              done = true;
-            } else {
-              if (g == 0) myrank[k].x = (uint32_t)M;
-              nrank = k + 1;
-              if (k == K) th = M >> 8;
-              if (k > K && (M >> 8) != th) done = true;   // one key past the run of rank K
+          M = group_max_key<G>(L[0]);
+          pop(M);
+          need = redo && L[0] == kKeyNone;
+          if (redo && g == 0) myrank[k] = (uint32_t)M;
+        }
+        if (redo) mK = M;
+      }
+      // Where the run of equal top 24 bits continues past rank K, its members for
+      // the ranks c..K are chosen among all of it: in a run the exact order is that
+      // of the scores' low bytes (the other way for negative scores), then of the
+      // indices, 16 bits that are kept as a float near 2.  A run of any length takes
+      // a list and a round per rank.  Layers of logits on a grid of quarters with a zero
+      // bias, before (runs extracted to their end into a buffer, ranks ordered by one
+      // lane's insertions, longer runs left to the exact 64-bit path) -> now, in us: E = 32
+      // K = 16 65,537 tokens 60.0 -> 35.7, 600,000 197 -> 119; E = 64 K = 16 4,097 tokens
+      // 48.9 -> 30.6; E = 16 K = 15 65,537 tokens 39.2 -> 32.7.
+      const bool ext = staged && rowflag != 0;
+      if (__any(ext)) {
+        lds_wave_sync();
+        int c = 0;
+#pragma unroll
+        for (int s = 0; s < HSLOT; ++s) {
+          const int k = s * G + g;
+          if (k <= K && ((uint32_t)myrank[k] ^ (uint32_t)mK) >= 256u) c = k + 1;
+        }
+        c = group_max_i32<G>(c);
+        lds_wave_sync();
+        const uint32_t flip = mK < 0 ? 0xFFu : 0u;
+        auto run_key = [&](float score, uint32_t ipk, int i) -> int {
+          const uint32_t sb = __float_as_uint(score);
+          const uint32_t low = __builtin_amdgcn_perm(sb ^ flip, ipk, 0x0C0C0400u | (uint32_t)i);
+          return (sb ^ (uint32_t)mK) < 256u ? (int)(low | 0x40000000u) : kKeyNone;
+        };
+        bool need = ext, more = false;
+        int M = kKeyTop;
+#pragma unroll 1
+        for (int k = c; __any(ext && k <= K); ++k) {
+          if (__any(need)) {
+            if (need) {
+              rebuild(zf, M, L, run_key);
+              more = L[kList - 1] != kKeyNone;
             }
           }
-        }
-        bad = bad || !done;
-      }
-      slow = slow || bad;
-      staged = staged && !slow;
-      lds_wave_sync();
-#pragma unroll
-      for (int s = 0; s < RSLOT; ++s) {
-        const int k = s * G + g;
-        if (staged && k < nrank) {
-          const int key = (int)myrank[k].x;
-          const int e = 255 - (key & 0xFF);
-          bool ok;
-          uint32_t zb = z_from_key(key, sh_bk[0][e], &ok);
-          if (!ok) zb = seg_z[t * E + e];
-          const uint32_t sb = __float_as_uint(__uint_as_float(zb << 16) + sh_b[e]);
-          myrank[k] = make_uint2(sb, (zb << 16) | (uint32_t)e);
+          M = group_max_key<G>(L[0]);
+          pop(M);
+          need = ext && more && L[0] == kKeyNone;
+          if (ext && g == 0 && k <= K) myrank[k] = ((uint32_t)mK & 0xFFFFFF00u) | ((uint32_t)M & 0xFFu);
         }
       }
       lds_wave_sync();
-    }
-
-    // ---- staged rows: sort the extracted ranks exactly where key order and
-    // exact order differ (only inside a run of equal top-24-bit keys)
-    // rank order of two staged entries: higher score, then lower expert
-    auto before = [](uint2 a, uint2 c) -> bool {
-      const float fa = __uint_as_float(a.x), fc = __uint_as_float(c.x);
-      return fa > fc || (fa == fc && (a.y & 0xFF) < (c.y & 0xFF));
-    };
-    if (__builtin_expect(__any(staged), 0)) {
-      bool coll = false;
+      // exact keys (z as recovered above where the rank kept its key), and each
+      // one's place: how many are greater
+      uint32_t ek[HSLOT], zs[HSLOT];
 #pragma unroll
-      for (int s = 0; s < RSLOT; ++s) {
+      for (int s = 0; s < HSLOT; ++s) {
         const int k = s * G + g;
-        if (staged && k + 1 < nrank) coll |= !before(myrank[k], myrank[k + 1]);
-      }
-      const bool coll_row = group_max_i32<G>((int)coll) != 0;
-      if (coll_row && g == 0) {
-        for (int i = 1; i < nrank; ++i) {
-          const uint2 v = myrank[i];
-          int j = i - 1;
-          while (j >= 0) {
-            const uint2 u = myrank[j];
-            if (!before(v, u)) break;
-            myrank[j + 1] = u;
-            --j;
-          }
-          myrank[j + 1] = v;
+        ek[s] = 0;
+        zs[s] = zown[s];
+        if (staged && k <= K) {
+          const int key = (int)(uint32_t)myrank[k];
+          ek[s] = min(255 - (key & 0xFF), E - 1);
+          bool ok = true;
+          if (key != rk[s]) zs[s] = z_from_key(key, sh_bk[0][ek[s]], &ok);
+          if (!ok) zs[s] = seg_z[t * E + ek[s]];
         }
+      }
+      uint64_t own[HSLOT];
+      uint32_t place[HSLOT];
+#pragma unroll
+      for (int s = 0; s < HSLOT; ++s) {
+        const int k = s * G + g;
+        own[s] = exact_key(__float_as_uint(__uint_as_float(zs[s] << 16) + sh_b[ek[s]]), ek[s], zs[s]);
+        place[s] = 0;
+        if (staged && k <= K) myrank[k] = own[s];
+      }
+      lds_wave_sync();
+#pragma unroll
+      for (int i = 0; i <= K; ++i) {
+        const uint64_t x = myrank[i];
+#pragma unroll
+        for (int s = 0; s < HSLOT; ++s) place[s] += x > own[s];
+      }
+      lds_wave_sync();
+#pragma unroll
+      for (int s = 0; s < HSLOT; ++s) {
+        if (staged && s * G + g <= K) myrank[place[s]] = own[s];
       }
       lds_wave_sync();
     }
@@ -615,8 +608,7 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
           }
           m = group_max_u64<G>(m);
           prevk = m;
-          if (g == 0)
-            myrank[k] = make_uint2(exact_key_sbits(m), (exact_key_z(m) << 16) | (uint32_t)exact_key_expert(m));
+          if (g == 0) myrank[k] = m;
         }
       }
       lds_wave_sync();
@@ -648,17 +640,17 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
     tv = group_bcast<G, K % G>(tv, g);
     if (valid && fromlds) {
 #pragma unroll
-      for (int s = 0; s < RSLOT; ++s) {
+      for (int s = 0; s < HSLOT; ++s) {
         const int k = s * G + g;
         if (k < K) {
-          const uint2 v = myrank[k];
-          const int e = (int)(v.y & 0xFF);
+          const uint64_t v = myrank[k];
+          const int e = exact_key_expert(v);
           at<int32_t>(seg_idx, (t * K + k) * 4u) = e;
-          at<float>(seg_score, (t * K + k) * 4u) = sigmoid_fast(__uint_as_float((v.y >> 16) << 16));
+          at<float>(seg_score, (t * K + k) * 4u) = sigmoid_fast(__uint_as_float(exact_key_z(v) << 16));
           if (load) atomicAdd(&sh_load[e], 1u);
         }
       }
-      tv = __uint_as_float(myrank[K].x);
+      tv = __uint_as_float(exact_key_sbits(myrank[K]));
     }
     if (valid && g == 0) at<float>(seg_tau, t * 4u) = tv;
 
