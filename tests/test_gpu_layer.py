@@ -111,24 +111,21 @@ def test_layer_equals_the_call_sequence(eqb):
         np.testing.assert_array_equal(got[k].view(np.uint32), ref[k].view(np.uint32))
 
 
-# The one-call layer's route sweep takes its last rows as dynamic tails
-# (chunks that each block's waves claim once their own range is done) when a
-# block's range is long; a grid cap makes the ranges long at sizes the oracle
-# finishes quickly.  Groups of up to 8 blocks per partition, one or several
-# groups, partitions of unequal size and the hard rows (dry lanes, ties,
-# equal logits) of the routing tests.
-DYNAMIC = [("large256", 131072, 1, 16), ("large256", 262144, 1, 40), ("large256", 196608, 5, 24),
+# Long block ranges, whose steps the waves of a block claim one after another; a
+# grid cap makes the ranges long at sizes the oracle finishes quickly.  Blocks
+# that lie in one partition and blocks that hold a boundary of unequal partitions.
+LONG = [("large256", 131072, 1, 16), ("large256", 262144, 1, 40), ("large256", 196608, 5, 24),
            ("skew64", 262144, 3, 24), ("split128", 262144, 2, 34)]
 CUTS = {2: [0.58], 3: [0.30, 0.71], 5: [0.13, 0.41, 0.62, 0.85]}   # unequal partitions
 
 
-@pytest.mark.parametrize("name,T,P,cap", DYNAMIC, ids=[f"{d[0]}-P{d[2]}-cap{d[3]}" for d in DYNAMIC])
-def test_layer_dynamic_tails(eqb, name, T, P, cap):
+@pytest.mark.parametrize("name,T,P,cap", LONG, ids=[f"{d[0]}-P{d[2]}-cap{d[3]}" for d in LONG])
+def test_layer_long_ranges(eqb, name, T, P, cap):
     w = W.WORKLOADS[name].with_T(T, P)
     z, b, off = W.generate(w)
     if P > 1:
         off = np.array([0] + [int(T * f) for f in CUTS[P]] + [T], np.int64)
-    say(f"dynamic tails {name} T={T} E={w.E} K={w.K} P={P} grid cap {cap}")
+    say(f"long ranges {name} T={T} E={w.E} K={w.K} P={P} grid cap {cap}")
     want = O.run_layer(z, b, w.K, off, threads=8)
     for got in run_twice(eqb, z, b, w.K, off, cap=cap):
         check(got, want, w.K)
@@ -171,26 +168,35 @@ def test_layer_long_blocks_add_fine_counts_to_slabs(eqb, P):
         check(got, want, w.K)
 
 
-# The layer's route sweep adds its coarse counts to 16-bit slab counters where
-# no slab can take more than 65,535 rows.  A grid cap of 96 gives 12 blocks per
-# slab (8 slabs per partition at P = 1, 4 at P = 2) and no dynamic tails; with
-# 5,461 rows per block a slab takes 65,532 rows (16-bit counters), with 5,462
-# it takes 65,544 (the 32-bit form).  Every column is one value, so each
-# expert's rows all land in one bin and that counter reaches its bound.
-LIMIT = [(5461, 1), (5462, 1), (5461, 2), (5462, 2)]
+# With images, the layer's route sweep spreads the counts outside their windows
+# over two slabs, of 16-bit counters where neither can take more than 65,535 rows:
+# with a grid cap of 96, 48 blocks' rows each, 65,520 at 1,365 rows per block and
+# 65,568 (the 32-bit form) at 1,366.  Every row is the same and every margin outside
+# the windows, so each expert's counter in either slab reaches that many.
+LIMIT = [(1365, 1), (1366, 1), (1365, 2), (1366, 2)]
+
+
+def columns(E):
+    """One value per expert, 64 apart: margins of 0 or of 64 and more."""
+    return W._to_bf16_bits((64.0 * np.random.default_rng(E).permutation(E) - 32.0 * E).astype(np.float32))
+
+
+def outside_the_windows(H):
+    """No count in the bins of margins from 2^-11 to 32 of either sign."""
+    raw = np.arange(256)
+    raw = np.where(raw & 0x80, raw ^ 0x80, raw ^ 0xFF)          # raw high byte of each kappa bin
+    return not H[:, ((raw & 0x7F) >= 0x3A) & ((raw & 0x7F) <= 0x41)].any()
 
 
 @pytest.mark.parametrize("rpb,P", LIMIT, ids=[f"rows{c[0]}-P{c[1]}" for c in LIMIT])
 def test_layer_coarse_counts_at_the_16bit_bound(eqb, rpb, P):
     T, E, K = 96 * rpb, 64, 4
-    rng = np.random.default_rng(rpb + P)
-    col = W._to_bf16_bits(rng.normal(0.0, 1.0, E).astype(np.float32))
-    z = np.broadcast_to(col, (T, E)).copy()
+    z = np.broadcast_to(columns(E), (T, E)).copy()
     b = np.zeros(E, np.float32)
     off = None if P == 1 else np.array([0, T // 2, T], np.int64)
     say(f"one value per column, T={T} E={E} K={K} P={P}, grid cap 96")
     want = O.run_layer(z, b, K, off, threads=8)
-    assert want["H"].max() == T
+    assert want["H"].max() == T and outside_the_windows(want["H"])
     for got in run_twice(eqb, z, b, K, off, cap=96):
         check(got, want, K)
 
@@ -213,7 +219,7 @@ def test_layer_runs_of_equal_rows(eqb, P):
 
 # Small layers of every expert count: a single row, a few rows (fewer than
 # one block step, so every block of the fine pass stores an image of almost
-# nothing), K up to E - 1 (the generic route kernel past K = 14), several
+# nothing), K up to E - 1 (the generic route kernel past K = 16), several
 # partitions.
 SMALL = [(8, 1, 1, 1), (8, 7, 17, 2), (16, 3, 1, 1), (16, 9, 2, 1), (16, 15, 4099, 3),
          (32, 5, 3, 2), (32, 31, 1001, 3), (64, 1, 1, 1), (64, 14, 65, 4), (256, 255, 3, 1),
@@ -244,8 +250,8 @@ def test_layer_random_shapes(eqb, i):
 @pytest.mark.parametrize("P", [1, 4])
 def test_layer_beyond_4gib_of_logits(eqb, P):
     """131 copies of a 65,536-token batch (E = 256): 8,585,216 tokens and
-    4.4 GB of logits, so offsets into z pass 2^32 bytes (dynamic tails and
-    per-block fine images at that size).  Each row's routing is its copy's,
+    4.4 GB of logits, so offsets into z pass 2^32 bytes (claimed steps and
+    per-block images of both counts at that size).  Each row's routing is its copy's,
     every count is 131 times the copy's (a partition's loads: its copies
     times the copy's), and the r-th largest key of 131 copies, r = 131 r_M, is
     the r_M-th of one copy: the quantile and the centred bias are the copy's,

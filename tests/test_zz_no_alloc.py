@@ -9,6 +9,8 @@ import pytest
 import torch
 
 import workloads as W
+from oracle import eqb_oracle as O
+from test_gpu_layer import columns
 
 pytestmark = pytest.mark.gpu
 
@@ -56,6 +58,9 @@ def run_both(eqb, name, T, P):
     return host(ref), host(got)
 
 
+LIMIT = [(5461, 1), (5462, 1), (5461, 2), (5462, 2)]
+
+
 def test_noalloc_layer_matches_the_workspace_layer(eqb):
     # two calls in a row on the shared scratch: a large layer, then a smaller
     # one (fewer partitions and experts), then the large one again
@@ -66,11 +71,9 @@ def test_noalloc_layer_matches_the_workspace_layer(eqb):
             np.testing.assert_array_equal(got[k].view(np.uint8), ref[k].view(np.uint8), err_msg=f"{name} {k}")
 
 
-def test_noalloc_layer_with_dynamic_tails(eqb):
-    # a grid of 16 blocks makes each block's range long enough for the route
-    # sweep's dynamic tails (claim counters in the scratch array, which the
-    # coarse selection resets); one partition, so 16 count slabs per
-    # partition; then a smaller layer and the first one again
+def test_noalloc_layer_long_ranges(eqb):
+    # a grid of 16 blocks, whose waves claim many steps; one partition, so 8 count
+    # slabs; then a smaller layer and the first one again
     try:
         eqb.eqb_set_max_blocks(16)
         for name, T, P in (("large256", 131072, 1), ("skew64", 7001, 4), ("large256", 131072, 1)):
@@ -80,6 +83,37 @@ def test_noalloc_layer_with_dynamic_tails(eqb):
                 np.testing.assert_array_equal(got[k].view(np.uint8), ref[k].view(np.uint8), err_msg=f"{name} {k}")
     finally:
         eqb.eqb_set_max_blocks(0)
+
+
+@pytest.mark.parametrize("rpb,P", LIMIT, ids=[f"rows{c[0]}-P{c[1]}" for c in LIMIT])
+def test_noalloc_coarse_counts_at_the_16bit_bound(eqb, rpb, P):
+    """Without images all coarse counts go to the slabs, 8 per partition at P = 1 and 4 at
+    P = 2: with a grid cap of 96, 12 blocks' rows each, 65,532 at 5,461 rows per block
+    (16-bit counters) and 65,544 (the 32-bit form) at 5,462.  Every row is the same, so
+    each expert's counter in every slab reaches that many."""
+    T, E, K = 96 * rpb, 64, 4
+    z = np.broadcast_to(columns(E), (T, E)).copy()
+    b = np.zeros(E, np.float32)
+    off = np.array([0, T] if P == 1 else [0, T // 2, T], np.int64)
+    want = O.run_layer(z, b, K, off, threads=8)
+    assert want["H"].max() == T
+    dev = torch.device("cuda:0")
+    o = outputs(eqb, T, E, K, P, dev)
+    say(f"noalloc, one value per column, T={T} P={P}, grid cap 96")
+    try:
+        eqb.eqb_set_max_blocks(96)
+        eqb.eqb_layer_noalloc(torch.from_numpy(z.view(np.int16)).to(dev), torch.from_numpy(b).to(dev), K, o["idx"],
+                              o["score"], o["tau"], o["load"], o["q"], o["b_next"], o["status"],
+                              eqb.PartOffsets([int(x) for x in off]), o["H"], o["L"])
+    finally:
+        eqb.eqb_set_max_blocks(0)
+    got = host(o)
+    assert int(got["status"][0]) == 0
+    for k in ("idx", "load", "H", "L"):
+        np.testing.assert_array_equal(got[k], want[k], err_msg=k)
+    for k, w in (("tau", "tau"), ("b_next", "b_next")):
+        np.testing.assert_array_equal(got[k].view(np.uint32), want[w].view(np.uint32), err_msg=k)
+    np.testing.assert_array_equal(got["q"].view(np.uint16), want["bhat"])
 
 
 def test_noalloc_layer_rejects_a_layer_beyond_its_scratch(eqb):
