@@ -114,7 +114,7 @@ def test_parity_full_size(eqb, name):
     for k in ("H", "L", "u", "v", "rho", "bhat", "b_next", "idx", "tau"):
         np.testing.assert_array_equal(one[k], got[k])
     np.testing.assert_array_equal(one["load"][0], got["load"].sum(0))
-    # the one-call layer (dynamic tails, several count slabs per partition),
+    # the one-call layer (per-block images, several count slabs per partition),
     # twice on one workspace, at the size and launch configuration the bench
     # times
     say(f"full {name}: one-call layer")
@@ -147,19 +147,25 @@ def test_every_E_and_K_extremes(eqb, E):
             assert_parity(gpu_layer(eqb, z, b, K, off), O.run_layer(z, b, K, off), K)
 
 
+LANES = {32: 4, 64: 4, 128: 8, 256: 8}       # lanes per row of the fast route kernel: lane (e >> 2) % LANES
+# Keys of its sorted list for the (E, K) below, as the kernel chooses them.
+LIST_DEPTH = {(32, 6): 7, (64, 6): 7, (64, 8): 7, (64, 14): 8, (128, 8): 5, (256, 6): 5, (256, 7): 5, (256, 8): 5,
+              (256, 11): 6, (256, 13): 7, (256, 16): 8}
+
+
 @pytest.mark.parametrize("E,K", [(64, 8), (64, 6), (128, 6), (256, 8), (256, 6)])
 def test_lists_run_dry(eqb, E, K):
     """Rows whose top ranks crowd into the experts of one lane.  The fast
-    route kernel keeps five keys per lane at E >= 64 (lane g of a row holds
-    the experts with (e >> 2) % 8 == g); a lane holding more of the top K+1
+    route kernel keeps five to nine keys per lane (lane g of a row holds
+    the experts with (e >> 2) % LANES[E] == g); a lane holding more of the top K+1
     keys runs dry, and the row is extracted again with refilled lists.  Some
     rows also carry exact ties, so dry rows meet the exact ordering of tied
     scores."""
     rng = np.random.default_rng(1000 + E + K)
     T = 3001
     x = rng.standard_normal((T, E)).astype(np.float32)
-    lane = (np.arange(E) >> 2) % 8
-    hot = rng.integers(0, 8, T)
+    lane = (np.arange(E) >> 2) % LANES[E]
+    hot = rng.integers(0, LANES[E], T)
     crowd = rng.random(T) < 0.6
     boost = np.where(crowd[:, None] & (lane[None, :] == hot[:, None]), np.float32(6.0), np.float32(0.0))
     x = x + boost
@@ -173,60 +179,58 @@ def test_lists_run_dry(eqb, E, K):
     assert_parity(gpu_layer(eqb, z, b, K, off), O.run_layer(z, b, K, off), K)
 
 
-@pytest.mark.parametrize("E,K", [(64, 6), (128, 8), (256, 8), (256, 6), (256, 7)])
+@pytest.mark.parametrize("E,K", sorted(LIST_DEPTH))
 def test_dry_lane_next_key(eqb, E, K):
-    """A lane of the fast kernel (five keys per lane at E >= 64; lane g holds
-    the experts with (e >> 2) % 8 == g) that holds exactly five of the top
-    K+1 keys pops its whole list; its next key is then found by a scan.
-    Each row puts five experts of one lane on top and the rest of the top K+1
-    in other lanes, and places that lane's sixth expert (a) far below rank
+    """A lane of the fast kernel that holds exactly as many of the top K+1 keys
+    as its list, D, pops its whole list; its next key is then found by a scan.
+    Each row puts D experts of one lane on top and the rest of the top K+1
+    in other lanes, and places that lane's next expert (a) far below rank
     K, (b) just below rank K, (c) on rank K's score (a tie that the lower
     index breaks), (d) just above rank K (the rounds missed it and the row is
-    extracted again), or (e) two binary32 ulps below rank K's score, sharing
-    its top 24 bits (the run past rank K continues)."""
+    extracted again), or (e) a few binary32 ulps below rank K's score, sharing
+    its top 24 bits (the run past rank K continues; a tie as in (c) where the
+    lane holds all of the top K+1)."""
+    D = LIST_DEPTH[E, K]
     rng = np.random.default_rng(4100 + E + K)
     T = 5 * 1200 + 7
-    lane = (np.arange(E) >> 2) % 8
+    lane = (np.arange(E) >> 2) % LANES[E]
     x = (rng.standard_normal((T, E)) * 0.5 - 3.0).astype(np.float32)
     # every expert outside lane 0 carries +2^-20: sums among them keep their
-    # ties, and a lane-0 expert on the same logit scores 2 ulps lower (the
-    # scores near rank K lie in [4, 8))
+    # ties, and a lane-0 expert on the same logit scores 1 to 4 ulps lower (the
+    # scores near rank K lie in [2, 16))
     b = np.where(lane == 0, np.float32(0.0), np.float32(2.0 ** -20)).astype(np.float32)
-    rank_k = np.float32(6.0 - 0.5 * (K - 5))
+    rank_k = np.float32(6.0 - 0.5 * (K - D)) if K >= D else np.float32(8.0)
     for t in range(T):
         c = t % 5
-        h = 0 if c == 4 else int(rng.integers(1, 8))
+        h = 0 if c == 4 else int(rng.integers(1, LANES[E]))
         mine = rng.permutation(np.flatnonzero(lane == h))
         other = rng.permutation(np.flatnonzero((lane != h) & (lane != 0)))
-        x[t, mine[:5]] = 8.0 + np.arange(5)[::-1]            # ranks 0..4, one lane
-        x[t, other[:K - 4]] = 6.0 - 0.5 * np.arange(K - 4)   # ranks 5..K, other lanes
-        x[t, mine[5]] = {0: -2.0, 1: rank_k - 0.25, 2: rank_k, 3: rank_k + 0.25, 4: rank_k}[c]
+        x[t, mine[:D]] = 8.0 + np.arange(D)[::-1]                    # ranks 0..D-1, one lane
+        x[t, other[:K + 1 - D]] = 6.0 - 0.5 * np.arange(K + 1 - D)   # ranks D..K, other lanes
+        x[t, mine[D]] = {0: -2.0, 1: rank_k - 0.25, 2: rank_k, 3: rank_k + 0.25, 4: rank_k}[c]
     z = O.f32_to_bf16_rne(x.astype(np.float32))
     off = np.array([0, T // 2, T], np.int64)
     say(f"dry lane next key E={E} K={K} T={T}")
     assert_parity(gpu_layer(eqb, z, b, K, off), O.run_layer(z, b, K, off), K)
 
 
-# Every routing kernel the library dispatches for E >= 64: the unrolled K = 2
-# kernel on an ordinary bias (its common path), the generic-K fast kernel
-# (extraction loop with list refills, G = 8 lanes per row) for the K it
-# serves, and the exact 64-bit kernel above K = 14 (Sec. 2 allows any
-# 1 <= K < E).
+# Routing kernels of E >= 64: fan-outs with a kernel of their own (up to K = 16),
+# and the exact 64-bit kernel beyond (Sec. 2 allows any 1 <= K < E).
 ROUTE_VARIANTS = [(E, K) for E in (64, 128, 256) for K in (3, 5, 7, 10, 14)] + \
-    [(64, 2), (256, 2), (256, 15), (256, 16)]
+    [(64, 2), (256, 2), (256, 15), (256, 16), (64, 17), (128, 20), (256, 17)]
 
 
 def _variant_inputs(E, K, T):
     """Skewed logits (per-expert offsets, an ordinary binary32 bias) with
     three kinds of hard rows mixed in: rows whose top ranks crowd into the
-    experts of one lane of the fast kernel (lane g holds (e >> 2) % 8 == g),
+    experts of one lane of the fast kernel (lane g holds (e >> 2) % LANES[E] == g),
     so its list runs dry; rows on a half-step grid, full of exact ties, also
     at the cutoff; and rows whose logits are all equal."""
     rng = np.random.default_rng(7000 + 17 * E + K)
     x = (rng.standard_normal((T, E)) + rng.standard_normal(E) * 0.7).astype(np.float32)
     kind = rng.random(T)
-    lane = (np.arange(E) >> 2) % 8
-    hot = rng.integers(0, 8, T)
+    lane = (np.arange(E) >> 2) % LANES[E]
+    hot = rng.integers(0, LANES[E], T)
     crowd = kind < 0.08
     x = x + np.where(crowd[:, None] & (lane[None, :] == hot[:, None]), np.float32(5.0), np.float32(0.0))
     grid = (kind >= 0.08) & (kind < 0.18)
