@@ -1,7 +1,7 @@
 """Benchmark: one MoE layer's routing + Exact Quantile Balancing statistics.
 
 A step is the whole path over one batch already resident in HBM, one call of
-eqb_layer (five kernels, no counter fill: the workspace is left zeroed):
+eqb_layer (four kernels, no counter fill: the workspace is left zeroed):
   route_topk + loads + coarse counts -> select pass 1 (clears the coarse
   counts) -> fine counts (pass 2) -> select pass 2 (clears the fine counts)
   -> centred bias and status.

@@ -240,8 +240,9 @@ eqb_status eqb_lei_inject(float* grad_s, const float* inj, int64_t T, int32_t E,
  *   where g[t,e] = grad_score[t,k] if e = topk_idx[t,k] (the gradient of the
  *   loss w.r.t. the mixture weight s_{t,e} of a selected expert) and 0 for the
  *   other experts; inj [P,E] from eqb_lei_residual, or NULL for the plain
- *   router backward.  sigmoid'(z) = e/(1+e)^2, e = exp(-|z|), in binary32
- *   (a few ulp); the sum and product are single binary32 operations.
+ *   router backward.  sigmoid'(z) = q - q^2, q = e/(1+e), e = exp(-|z|), in
+ *   binary32 (a few ulp, whatever the size of z); the sum and product are single
+ *   binary32 operations.
  *   z [T,E] bf16 bits (16-byte aligned), topk_idx [T,K] int32, grad_score
  *   [T,K] binary32 (in); grad_z [T,E] binary32 (out, 16-byte aligned).
  *   Index entries outside [0, E) are ignored.
@@ -254,7 +255,7 @@ eqb_status eqb_lei_router_backward(const uint16_t* z, const int32_t* topk_idx, c
  * One whole layer in one call (Sec. 2, Eq. 1 and "Quantile Balancing";
  * Appendix C, Algorithm 1 steps 1-6; Eq. 2): routing with the fused coarse
  * counts, the coarse selection, the fine counts and the fine selection with
- * the centred bias, enqueued as five kernels on `stream`.  It computes what
+ * the centred bias, enqueued as four kernels on `stream`.  It computes what
  * eqb_route_topk, eqb_select_quantile(1), eqb_margin_hist_pass2 and
  * eqb_select_quantile(2) compute in sequence, with r = eqb_rank(T, K, E).
  *   z [T,E] bf16 bits, b [E] binary32                       (in)
@@ -271,8 +272,9 @@ eqb_status eqb_lei_router_backward(const uint16_t* z, const int32_t* topk_idx, c
  *     counts and the selections while the layer runs: they must be ALL ZERO
  *     when the call's work starts, and the call's work leaves them all zero
  *     again (each selection clears the counts it has summed).  The rest is
- *     scratch for the fine pass's per-block count images, which every call
- *     overwrites before reading; its contents do not matter.  So a caller
+ *     scratch for the per-block count images of the routing and then of the
+ *     fine pass, which every call overwrites before reading; its contents do not
+ *     matter.  So a caller
  *     zeroes the workspace once after allocating it and may then run layer
  *     after layer with it.  After an error reported by the call or by the
  *     runtime while its work ran, zero it again before the next use.  Two
@@ -300,8 +302,8 @@ eqb_status eqb_layer(const uint16_t* z, const float* b, int64_t T, int32_t E, in
  * live in a library-owned device array of EQB_NOALLOC_SCRATCH_BYTES per GPU
  * (held until the process ends) instead of a caller workspace.  The call
  * allocates nothing; the caller still passes every input and output.
- *   The array holds the layer's counters only (the fine pass adds its counts
- *   to the partition slabs instead of storing per-block images).
+ *   The array holds the layer's counters only (routing and fine pass add all
+ *   their counts to the partition slabs instead of storing per-block images).
  *   Limit: eqb_layer_workspace_zero_bytes(E, P) <= EQB_NOALLOC_SCRATCH_BYTES,
  *   i.e. P * E <= 4096 (E = 256: up to 16 partitions); larger layers return
  *   EQB_ERR_SCRATCH before anything is enqueued.

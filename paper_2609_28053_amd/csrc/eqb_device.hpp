@@ -50,7 +50,7 @@ constexpr int kWinLo = 0x3A;
 static_assert(kWinLo % 2 == 0, "whole pairs of bins");
 __host__ __device__ constexpr int64_t win_words(int E) { return (int64_t)(E / 2) * kWinBins; }
 __device__ __forceinline__ int win_raw(int b) { return ((b & 8) << 4) | (kWinLo + (b & 7)); }
-// the i-th of the 128 pairs (2j, 2j + 1) of raw bytes that lie outside the window
+// the i-th of the 120 pairs (2j, 2j + 1) of raw bytes that lie outside the window
 __device__ __forceinline__ int outside_pair(int i) {
   const int half = (kNBins - kWinBins) / 4, j = i % half;
   return i / half * (kNBins / 4) + (j < kWinLo / 2 ? j : j + kWinBins / 4);
@@ -98,6 +98,20 @@ __device__ __forceinline__ float exp_neg_bf16(float a) {
   return __builtin_fmaf(-e1, a * kLoLn2, e1);
 }
 
+// The same of any BF16 a >= 0.  From a = 32 the second factor is 1 - c + c^2/2 (off by
+// c^3/6 < 5e-11 up to a = 128, where the result is 0).  From a = 64 the hardware
+// exponential, which has no subnormal results, gives 2^64 times the value (the
+// argument's sum is exact), and the scaling rounds once.
+__device__ __forceinline__ float exp_neg_bf16_wide(float a) {
+  const float kHi = 1.44268798828125f;
+  const float kLoLn2 = 4.888495368504664e-06f;
+  a = a > 128.0f ? 128.0f : a;
+  const bool up = a >= 64.0f;
+  const float c = a * kLoLn2, h = a >= kSigmoidMax ? -0.5f : 0.0f;
+  const float e1 = __builtin_amdgcn_exp2f((up ? 64.0f : 0.0f) - a * kHi);
+  return __builtin_amdgcn_ldexpf(__builtin_fmaf(-e1, __builtin_fmaf(c * h, c, c), e1), up ? -64 : 0);
+}
+
 // sigmoid(x) of a BF16 x: 1 / (1 + e) for x >= 0 and e / (1 + e) for x < 0, e =
 // exp(-|x|).  The hardware reciprocal r0 (1 ulp) of d = fl(1 + e) takes one
 // Newton step for 1 + e itself: what d lost, e - (d - 1), is exact (d in [1, 2]).
@@ -113,18 +127,10 @@ __device__ __forceinline__ float sigmoid_fast(float x) {
   return x >= 0.0f ? r : e * r;
 }
 
-// The same of any BF16 a >= 0.  From a = 32 the second factor is 1 - c + c^2/2 (off by
-// c^3/6 < 5e-11 up to a = 128, where the result is 0).  From a = 64 the hardware
-// exponential, which has no subnormal results, gives 2^64 times the value (the
-// argument's sum is exact), and the scaling rounds once.
-__device__ __forceinline__ float exp_neg_bf16_wide(float a) {
-  const float kHi = 1.44268798828125f;
-  const float kLoLn2 = 4.888495368504664e-06f;
-  a = a > 128.0f ? 128.0f : a;
-  const bool up = a >= 64.0f;
-  const float c = a * kLoLn2, h = a >= kSigmoidMax ? -0.5f : 0.0f;
-  const float e1 = __builtin_amdgcn_exp2f((up ? 64.0f : 0.0f) - a * kHi);
-  return __builtin_amdgcn_ldexpf(__builtin_fmaf(-e1, __builtin_fmaf(c * h, c, c), e1), up ? -64 : 0);
+__device__ __forceinline__ float max3_abs(float m, float a, float b) {
+  float r;
+  asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(m), "v"(a), "v"(b));
+  return r;
 }
 
 // sigmoid'(x) = e / (1 + e)^2, e = exp(-|x|), of a BF16 x with |x| < 32, in 12
@@ -132,11 +138,6 @@ __device__ __forceinline__ float exp_neg_bf16_wide(float a) {
 // 1 + e lies in [1, 2]: the hardware reciprocal (1 ulp) and one Newton step round
 // like the division but for rare last bits, and with q = sigmoid(-a), q - q^2 in
 // one rounding halves what q carries near 0.
-__device__ __forceinline__ float max3_abs(float m, float a, float b) {
-  float r;
-  asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(m), "v"(a), "v"(b));
-  return r;
-}
 // wide: any BF16 x, in 20 instructions; for |x| < 32 the same value.
 template <bool wide>
 __device__ __forceinline__ float sigmoid_prime_bf16(float x) {
@@ -206,12 +207,6 @@ __device__ __forceinline__ uint64_t group_max_u64(uint64_t m) {
     m = o > m ? o : m;
   }
   return m;
-}
-
-__device__ __forceinline__ int med3_i32(int a, int b, int c) {
-  int r;
-  asm volatile("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
 }
 
 // ------------------------------------------------------- float keys --
@@ -326,14 +321,13 @@ __device__ __forceinline__ void slab_clear(int32_t* __restrict__ hist, int P, in
 // Calls f(p, s0, s1) for every piece of [r0, r1) lying in one partition and
 // holding at most kSegMax rows.  Uniform across the block.
 template <class F>
-__device__ __forceinline__ void for_each_segment(int64_t r0, int64_t r1, const PartTable& pt, F&& f,
-                                                 int64_t seg_max = kSegMax) {
+__device__ __forceinline__ void for_each_segment(int64_t r0, int64_t r1, const PartTable& pt, F&& f) {
   int p = 0;
   int64_t t = r0;
   while (t < r1) {
     while (p < pt.P - 1 && pt.off[p + 1] <= t) ++p;
     int64_t end = pt.off[p + 1] < r1 ? pt.off[p + 1] : r1;
-    if (end - t > seg_max) end = t + seg_max;
+    if (end - t > kSegMax) end = t + kSegMax;
     f(p, t, end);
     t = end;
   }
@@ -341,14 +335,13 @@ __device__ __forceinline__ void for_each_segment(int64_t r0, int64_t r1, const P
 
 // The same pieces in reverse order (last rows first).
 template <class F>
-__device__ __forceinline__ void for_each_segment_rev(int64_t r0, int64_t r1, const PartTable& pt, F&& f,
-                                                     int64_t seg_max = kSegMax) {
+__device__ __forceinline__ void for_each_segment_rev(int64_t r0, int64_t r1, const PartTable& pt, F&& f) {
   int p = pt.P - 1;
   int64_t t = r1;
   while (t > r0) {
     while (p > 0 && pt.off[p] >= t) --p;
     int64_t start = pt.off[p] > r0 ? pt.off[p] : r0;
-    if (t - start > seg_max) start = t - seg_max;
+    if (t - start > kSegMax) start = t - kSegMax;
     f(p, start, t);
     t = start;
   }
@@ -439,7 +432,6 @@ __device__ __forceinline__ void flush_hist(uint32_t* sh, int32_t* __restrict__ s
 __device__ __forceinline__ uint32_t hist_row(int e) { return (uint32_t)(e >> 1) * kHistStride; }
 __device__ __forceinline__ uint32_t hist_inc(int e) { return 1u << ((e & 1) * 16); }
 
-// Rows handled by block blockIdx.x.
 // A 64-bit value every lane of the wave holds, moved to scalar registers.
 // Offsets of segment bases pass through it, so that the compiler knows the
 // bases are wave-uniform: loads and stores then take a 64-bit scalar base
@@ -450,6 +442,7 @@ __device__ __forceinline__ int64_t wave_uniform(int64_t x) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// Rows handled by block blockIdx.x.
 __device__ __forceinline__ void block_rows(int64_t T, int64_t rows_per_block, int64_t* r0, int64_t* r1) {
   *r0 = (int64_t)blockIdx.x * rows_per_block;
   *r1 = (*r0 + rows_per_block < T) ? *r0 + rows_per_block : T;

@@ -125,7 +125,7 @@ inline int layer_replicas(int P) { return P >= 8 ? 1 : 8 / P; }
 // Working buffers of one layer (eqb_layer): the per-partition coarse and
 // fine counts (layer_replicas(P) slabs per partition), the loads as the
 // route kernel accumulates them, the selections, and (optionally) room for
-// the fine pass's per-block count images.  Each piece starts on a 256-byte
+// the per-block count images.  Each piece starts on a 256-byte
 // boundary.  The counters (everything before the images) are zero when a
 // layer starts and zero again when it ends: the selection that reads a
 // counter clears it.  The images are scratch: the route sweep and after it the
@@ -159,7 +159,7 @@ inline size_t layer_workspace(void* base, int E, int P, LayerWorkspace* w, bool 
   const size_t load = align256((size_t)P * E * sizeof(int32_t));
   const size_t sel = align256((size_t)E * sizeof(int32_t));
   const size_t rib = align256((size_t)E * sizeof(int64_t));
-  const size_t zero = 2 * hist + load + 2 * sel + rib + kTicketBytes;
+  const size_t zero = 2 * hist + load + 2 * sel + rib + kTicketBytes;   // the second sel is not used
   const size_t part = with_part ? align256((size_t)layer_part_blocks(E) * part_words(E) * sizeof(uint32_t)) : 0;
   if (base && w) {
     char* p = static_cast<char*>(base);
@@ -204,9 +204,10 @@ int max_blocks_cap();
 
 // Blocks and rows per block for a streaming kernel over T rows: at most
 // blocks_per_cu blocks per CU, each owning a contiguous range of
-// ceil(T / blocks) rows (the last may be shorter), and at least min_rows rows
-// per block where T allows (a block's fixed costs, zeroing and flushing its
-// LDS counts, then pay for more rows).  With slices > 1 every row range is
+// ceil(T / blocks) rows (the last may be shorter), and no more than ceil(T /
+// min_rows) blocks (a block's fixed costs, zeroing and flushing its LDS counts,
+// then pay for more rows; just past a multiple of min_rows a block's share is up to
+// half of it smaller: 1,025 rows at 1,024 are blocks of 513).  With slices > 1 every row range is
 // shared by that many blocks, and *blocks counts the ranges.  The ranges are
 // not rounded to whole steps: with P equal partitions and a block count that P
 // divides, every partition boundary then falls on a block boundary, and no

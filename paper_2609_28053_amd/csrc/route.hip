@@ -32,8 +32,8 @@
 
 namespace eqb {
 
-// Widest fan-out of the fast kernel.  Every fan-out is a kernel of its own per E, about
-// 80 KB of code at E = 256, and no configuration here routes to more than 16 experts; neither
+// Widest fan-out of the fast kernel.  Every fan-out is a kernel of its own per E, 46 to
+// 71 KB of code at E = 256, and no configuration here routes to more than 16 experts; neither
 // LDS nor registers set the line.  65,537 tokens of E = 256: K = 16 53 us, K = 17 (generic
 // kernel) 171.
 constexpr int kFastKmax = 16;

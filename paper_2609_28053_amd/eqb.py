@@ -422,7 +422,7 @@ class Layer:
             self.status = torch.empty(1, dtype=torch.int32, device=dev)
 
     def step(self, z, b, part_off=None, sums=False, marks=None, stream=None):
-        """One layer through eqb_layer: one C call, five kernels, no fill of
+        """One layer through eqb_layer: one C call, four kernels, no fill of
         counters (the workspace comes back zeroed).  Writes topk_idx,
         topk_score, tau, load_out, q_bf16, b_next, status and, with sums=True,
         the summed counts H and L.  marks: see layer_marks."""

@@ -3,7 +3,7 @@
 eqb_layer chains the route kernel, both selections and the fine pass with a
 caller-owned workspace whose counter part must be zero when a layer starts
 and is left zero when it ends (each selection clears the counts it has
-summed); the rest is scratch for the fine pass's per-block count images.
+summed); the rest is scratch for the per-block count images.
 Every layer below runs twice on the same workspace: the second run can only
 match the oracle if the first left the counters zeroed.
 """
@@ -133,7 +133,7 @@ def test_layer_long_ranges(eqb, name, T, P, cap):
 
 def test_layer_scratch_contents_do_not_matter(eqb):
     """Past eqb_layer_workspace_zero_bytes the workspace is scratch for the
-    fine pass's per-block count images: filled with ones before each call,
+    per-block count images of both passes: filled with ones before each call,
     the layer still matches the oracle and leaves its counters zero."""
     w = W.WORKLOADS["split128"].with_T(40009, 3)
     z, b, off = W.generate(w)
