@@ -304,8 +304,8 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
     return (int)__builtin_amdgcn_perm(__float_as_uint(score), ipk, 0x07060500u | (uint32_t)i);
   };
 
-  // Rebuild a lane's sorted list from the values key(sum, index bytes, i) of its
-  // experts that are strictly below thr.
+  // Rebuild a lane's sorted list from the values key(sum, index bytes, i, &in) of its
+  // experts that are in and strictly below thr.
   auto rebuild = [&](const float (&zf)[N], int thr, int (&L)[kList], auto&& key) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < kList; ++j) L[j] = kKeyNone;
@@ -315,8 +315,9 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
       const uint32_t ipk = idxpk(q);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int x = key(zf[q * 4 + i] + pick(bq, i), ipk, i);
-        list_insert(L, key_lt(x, thr) ? x : kKeyNone);
+        bool in = true;
+        const int x = key(zf[q * 4 + i] + pick(bq, i), ipk, i, &in);
+        list_insert(L, (in & key_lt(x, thr)) ? x : kKeyNone);
       }
       __builtin_amdgcn_sched_barrier(0);   // one piece's keys and biases at a time: registers
     }
@@ -494,7 +495,7 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
 #pragma unroll 1
         for (int k = 0; k <= K; ++k) {
           if (__any(need)) {
-            if (need) rebuild(zf, M, L, key_of);
+            if (need) rebuild(zf, M, L, [&](float score, uint32_t ipk, int i, bool*) { return key_of(score, ipk, i); });
           }
           M = group_max_key<G>(L[0]);
           pop(M);
@@ -506,12 +507,12 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
       // Where the run of equal top 24 bits continues past rank K, its members for
       // the ranks c..K are chosen among all of it: in a run the exact order is that
       // of the scores' low bytes (the other way for negative scores), then of the
-      // indices, 16 bits that are kept as a float near 2.  A run of any length takes
+      // indices, 16 bits that are kept as a subnormal float.  A run of any length takes
       // a list and a round per rank.  Layers of logits on a grid of quarters with a zero
       // bias, before (runs extracted to their end into a buffer, ranks ordered by one
       // lane's insertions, longer runs left to the exact 64-bit path) -> now, in us: E = 32
-      // K = 16 65,537 tokens 60.0 -> 35.7, 600,000 197 -> 119; E = 64 K = 16 4,097 tokens
-      // 48.9 -> 30.6; E = 16 K = 15 65,537 tokens 39.2 -> 32.7.
+      // K = 16 65,537 tokens 60.0 -> 35.6, 600,000 197 -> 118; E = 64 K = 16 4,097 tokens
+      // 48.9 -> 30.3; E = 16 K = 15 65,537 tokens 39.2 -> 32.8.
       const bool ext = staged && rowflag != 0;
       if (__any(ext)) {
         lds_wave_sync();
@@ -523,11 +524,12 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
         }
         c = group_max_i32<G>(c);
         lds_wave_sync();
-        const uint32_t flip = mK < 0 ? 0xFFu : 0u;
-        auto run_key = [&](float score, uint32_t ipk, int i) -> int {
-          const uint32_t sb = __float_as_uint(score);
-          const uint32_t low = __builtin_amdgcn_perm(sb ^ flip, ipk, 0x0C0C0400u | (uint32_t)i);
-          return (sb ^ (uint32_t)mK) < 256u ? (int)(low | 0x40000000u) : kKeyNone;
+        const uint32_t top = ((uint32_t)mK & 0xFFFFFF00u) | (mK < 0 ? 0xFFu : 0u);
+        auto run_key = [&](float score, uint32_t ipk, int i, bool* in) -> int {
+          const uint32_t low = __float_as_uint(score) ^ top;     // below 256: of the run
+          const int x = (int)__builtin_amdgcn_perm(low, ipk, 0x0C0C0400u | (uint32_t)i);
+          *in = low < 256u;
+          return x;
         };
         bool need = ext, more = false;
         int M = kKeyTop;
@@ -572,18 +574,31 @@ __global__ __launch_bounds__(kRouteBlock) void route_fast_kernel(
         if (staged && k <= K) myrank[k] = own[s];
       }
       lds_wave_sync();
+      // A rank that the next one exceeds?  4,194,304 tokens of E = 256 with ties in order
+      // 1332 us without the look, 1265 with it; with more ranks a lane it does not pay
+      // (E = 16, K = 15, 65,537 tokens of ties 33.0 without, 33.5 with).
+      bool coll = HSLOT > 4;
+      if constexpr (HSLOT <= 4) {
 #pragma unroll
-      for (int i = 0; i <= K; ++i) {
-        const uint64_t x = myrank[i];
-#pragma unroll
-        for (int s = 0; s < HSLOT; ++s) place[s] += x > own[s];
+        for (int s = 0; s < HSLOT; ++s) {
+          const int k = s * G + g;
+          if (staged && k < K) coll |= myrank[k + 1] > own[s];
+        }
       }
-      lds_wave_sync();
+      if (__any(coll)) {
 #pragma unroll
-      for (int s = 0; s < HSLOT; ++s) {
-        if (staged && s * G + g <= K) myrank[place[s]] = own[s];
+        for (int i = 0; i <= K; ++i) {
+          const uint64_t x = myrank[i];
+#pragma unroll
+          for (int s = 0; s < HSLOT; ++s) place[s] += x > own[s];
+        }
+        lds_wave_sync();
+#pragma unroll
+        for (int s = 0; s < HSLOT; ++s) {
+          if (staged && s * G + g <= K) myrank[place[s]] = own[s];
+        }
+        lds_wave_sync();
       }
-      lds_wave_sync();
     }
 
     // ---- exact 64-bit extraction for rows flagged slow
