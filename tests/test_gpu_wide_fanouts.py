@@ -14,7 +14,7 @@ import workloads as W
 from oracle import eqb_oracle as O
 from test_gpu_fanouts import LANES
 from test_gpu_layer import check, eqb, run_twice, say  # noqa: F401 (eqb is a fixture)
-from timing import median_us
+from timing import least_us
 
 pytestmark = pytest.mark.gpu
 
@@ -76,9 +76,7 @@ def test_ties_cost_no_more_than_the_generic_kernel(eqb, E, T):  # noqa: F811
     g.manual_seed(E)
     z = (torch.randint(-16, 17, (T, E), generator=g, device="cuda") / 4).to(torch.bfloat16).view(torch.int16)
     b = torch.zeros(E, device="cuda")
-    us = {}
-    for K in (15, 16, 17):
-        lay = eqb.Layer(T, E, K)
-        us[K] = median_us(lambda: lay.step(z, b))
+    layers = {K: eqb.Layer(T, E, K) for K in (15, 16, 17)}
+    us = dict(zip(layers, least_us([lambda lay=lay: lay.step(z, b) for lay in layers.values()])))
     say(f"ties E={E} T={T}: " + ", ".join(f"K={K} {t:.1f} us" for K, t in us.items()))
     assert max(us[15], us[16]) <= 1.05 * us[17]
